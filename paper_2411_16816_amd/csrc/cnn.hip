@@ -8,22 +8,22 @@
 //   (M, b) = W_out h_2 + b_out,  I = M * F_rgb + b
 //
 // Activations are NHWC float32 with 32 channels.  The 3x3 convolutions are dense contractions
-// (K = 9 taps x 32 channels per output) and run on the matrix cores: v_mfma_f32_16x16x4_f32
-// (FP32 in, FP32 accumulate, so results match an FP32 reference to rounding).
-//   * forward / input-gradient convolution (k_conv3x3): a workgroup computes a 16 x 16-pixel
-//     tile for all 32 output channels from its 18 x 18 input halo staged in LDS; each wavefront
-//     owns 4 pixel rows.  In an MFMA the A operand is 16 pixels x 4 channels, the B operand 4
-//     channels x 16 output channels; the contraction order inside a tap is permuted so that a
-//     lane's eight A values of a tap are eight consecutive channels of one pixel (two 16-byte
-//     LDS reads), with B loaded to match.  The input gradient is the same convolution over the
-//     output gradient with the weights flipped and transposed (read in place, not copied).
-//   * weight gradient (k_conv3x3_wgrad): dW[tap][ci][co] = sum_p x[p + tap][ci] dy[p][co] is a
-//     contraction over pixels; persistent workgroups stage 8 x 16-pixel tiles (and the input
-//     halo) in LDS, each wavefront accumulates 9 of the 36 (tap, 16 ci, 16 co) output blocks in
-//     registers, and a second kernel adds the workgroups' partial sums in a fixed order.
+// (K = 9 taps x 32 channels per output) and run on the matrix cores, FP32 in and FP32 accumulate:
+//   * forward (k_conv3x3): v_mfma_f32_16x16x4_f32, whose results the ReLU decisions of the adjoint
+//     depend on (a change of rounding here flips some of them).  1920 x 1080, per convolution:
+//     0.354 ms, 108 TFLOP/s of the 137 that the instruction reaches from registers; as three
+//     independent workgroups per compute unit it took 0.46 ms.  The epilogue also leaves the signs
+//     of the activations (a bit per channel) for the adjoint, which would otherwise read the whole
+//     activation image for them;
+//   * input gradient (k_conv3x3_bwd) and weight gradient (k_conv3x3_wgrad): the bf16 matrix
+//     instructions on operands split into three bf16 parts (see below).  1920 x 1080: 0.22 ms
+//     (0.46 with the FP32 instructions) and 0.23 ms (0.445) per convolution.  Their matrix work alone
+//     is 0.095 ms and their HBM traffic about 0.12 ms; what they cannot overlap is the splitting and
+//     the barriers of one workgroup per compute unit;
 //   * the stem input, the 1x1 head and their adjoints are per-pixel kernels.
 #include "kernels.hpp"
 #include "reduce.hpp"
+#include "wave_ops.hpp"
 
 namespace splat {
 
@@ -38,34 +38,68 @@ constexpr int kCnnBlock = 128;               // per-pixel kernels with LDS contr
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// Stages an R x Cw pixel window of a 32-channel NHWC image whose top-left pixel is (y0, x0) into
-// LDS rows of kLS floats (zeros outside the image).  Every load of a thread is issued before its
-// first LDS store, so the window's global loads are all in flight at once.
-template <int R, int Cw>
-__device__ __forceinline__ void stage_window(const float* __restrict__ img, int H, int W, int y0, int x0, float* dst) {
-  constexpr int kVec = R * Cw * 8;
-  constexpr int kPer = (kVec + 255) / 256;
-  float4 v[kPer];
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int i = threadIdx.x + 256 * j;
-    v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < kVec) {
-      const int pix = i >> 3, q = i & 7;
-      const int y = y0 + pix / Cw, x = x0 + pix % Cw;
-      if (y >= 0 && y < H && x >= 0 && x < W) v[j] = reinterpret_cast<const float4*>(img + ((int64_t)y * W + x) * 32)[q];
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int i = threadIdx.x + 256 * j;
-    if (i < kVec) *reinterpret_cast<float4*>(&dst[(i >> 3) * kLS + (i & 7) * 4]) = v[j];
-  }
-}
-
 __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+
+// ---- FP32 contractions on the bf16 matrix cores ------------------------------------------------
+// A float is the exact sum of three bf16 values (8 significand bits each, rounded to nearest: the
+// remainders are exact): x = h + m + l.  A product of two floats is then the six products
+// hh + hm + mh + mm + hl + lh up to 2^-24 of it, each exact in FP32; v_mfma_f32_32x32x16_bf16 adds
+// sixteen of them per output in FP32.  Its rate is 17.5x that of the FP32 matrix instructions
+// (2400 against 137 TFLOP/s measured from registers), so six products are 2.9x as fast.
+//
+// The instruction rounds its sums of mixed magnitudes downwards: with all six products in one
+// accumulator a dot product of 288 normal values errs by 2.5e-7 rms of its own rms (FP32
+// instructions: 3.0e-7), of which -1.7e-8 is a bias that sums over many pixels would collect.  With
+// the hh products, which align, in an accumulator of their own the error is 9.5e-8 and the bias below
+// 1e-9.  Where the registers do not allow that, half of the terms are contracted negated and
+// subtracted, so that the bias cancels.  Infinities, NaN and magnitudes near the type's limits do not
+// split; the kernels find them and contract those outputs in plain FP32.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
+}
+
+// parts[0..2] = the (high, middle, low) bf16 parts of the pair (a, b), a in the low half
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t (&parts)[3]) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    parts[p] = pack_bf16(a, b);
+    a -= __uint_as_float(parts[p] << 16);
+    b -= __uint_as_float(parts[p] & 0xFFFF0000u);
+  }
+}
+
+__device__ __forceinline__ floatx16 mfma16(uint4 a, uint4 b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// the six products of a split contraction: part of A, part of B, and the accumulator of a kernel that
+// keeps one per magnitude (0: hl lh mm, 1: hm mh, 2: hh); two products on one are far apart
+constexpr int kProd = 6;
+__device__ constexpr int prod_a(int i) { return i == 0 ? 0 : i == 1 ? 0 : i == 2 ? 0 : i == 3 ? 2 : i == 4 ? 1 : 1; }
+__device__ constexpr int prod_b(int i) { return i == 0 ? 2 : i == 1 ? 1 : i == 2 ? 0 : i == 3 ? 0 : i == 4 ? 0 : 1; }
+__device__ constexpr int prod_acc(int i) { return i == 0 ? 0 : i == 1 ? 1 : i == 2 ? 2 : i == 3 ? 0 : i == 4 ? 1 : 0; }
+
+// 16-byte image loads through a buffer descriptor: an offset past its size reads zeros, so pixels
+// outside the image cost a select instead of a branch around each load.  The window starts at pixel
+// row y0 of a 32-channel image (rows before the image are only ever given the outside offset).
+struct Window {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ Window(const float* img, int W, int y0, int rows) {
+    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(img + (int64_t)y0 * W * 32), 0, rows * W * 128, 0x00027000);
+  }
+  __device__ __forceinline__ float4 load(bool inside, int offset) const {
+    return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, inside ? offset : -1, 0, 0));
+  }
+};
+
+// a window's bytes stay below 2^31 up to this width; wider images take k_conv_plain
+constexpr int kMaxWidth = 900000;
 
 struct ConvArgs {
   const float* in;      // [H*W][32]
@@ -75,8 +109,8 @@ struct ConvArgs {
   int transpose;        // 0: out[co] = sum w[co][ci][t] in[p + t][ci]; 1: input gradient
   const float* bias;    // [co_n] or null
   const float* addend;  // [H*W][32] or null, added before the activation
-  const float* mask;    // [H*W][32] or null: out = v where mask > 0, else 0
-  int relu;
+  uint32_t* bits_out;       // [H*W] or null: bit c of a pixel = out[c] > 0
+  const uint32_t* mask;     // [H*W] or null: out = v where the channel's bit is set, else 0
   int H, W;
 };
 
@@ -92,148 +126,540 @@ __device__ __forceinline__ float conv_w(const ConvArgs& a, int cin, int cout, in
   return a.w[((cin * a.ci_n + cout) * 3 + (2 - ky)) * 3 + (2 - kx)];
 }
 
-constexpr int kFrag = 9 * 8 * 2 * 64;   // B fragments of one convolution: [tap][step][half][lane]
+constexpr int kFrag = 9 * 16 * 64;           // A fragments of one convolution: [tap][quad][lane][4]
+constexpr int kSplitFrag = 9 * 2 * 3 * 64;   // A fragments (16 bytes) of one split convolution:
+                                             // [tap][channel half][part][lane]
+constexpr int kConvs = 5;                    // convolutions of the network
 
-// The B operands of every MFMA of k_conv3x3 in lane order, so that the convolution loads each
-// tap's fragments as coalesced rows (and flips / transposes the weights for the input gradient
-// here, once per launch, instead of per load).
-__global__ void k_conv_frag(ConvArgs a, float* __restrict__ frag) {
+struct ConvWeights {
+  const float* w[kConvs];
+  int ci_n[kConvs];
+};
+
+// The A operands of every MFMA of k_conv3x3 in lane order (quad: output half x four of the eight
+// contraction steps); all five convolutions in one launch (blockIdx.y).
+__global__ void k_conv_frag(ConvWeights cw, float* __restrict__ frag) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= kFrag) return;
-  const int lane = i & 63, h = (i >> 6) & 1, s = (i >> 7) & 7, tap = i >> 10;
-  frag[i] = conv_w(a, 8 * (lane >> 4) + s, 16 * h + (lane & 15), tap / 3, tap % 3);
+  const ConvArgs a{nullptr, nullptr, cw.w[blockIdx.y], cw.ci_n[blockIdx.y], kCC, 0};
+  const int lane = (i >> 2) & 63, q = (i >> 8) & 3, tap = i >> 10;
+  const int h = q >> 1, s = 4 * (q & 1) + (i & 3);
+  frag[blockIdx.y * kFrag + i] = conv_w(a, 8 * (lane >> 4) + s, 16 * h + (lane & 15), tap / 3, tap % 3);
 }
 
-__global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a, const float* __restrict__ frag) {
-  __shared__ __align__(16) float s_in[kHalo * kHalo * kLS];
-  const int tiles_x = (a.W + kTS - 1) / kTS;
-  const int tx0 = (int)(blockIdx.x % tiles_x) * kTS, ty0 = (int)(blockIdx.x / tiles_x) * kTS;
-  stage_window<kHalo, kHalo>(a.in, a.H, a.W, ty0 - 1, tx0 - 1, s_in);
-  __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int li = lane & 15, lk = lane >> 4;
-  floatx4 acc[4][2];
+// The split A operands (flipped, transposed weights) of every MFMA of k_conv3x3_bwd in lane
+// order, all five input-gradient convolutions in one launch (blockIdx.y).
+__global__ void k_conv_split_frag(ConvWeights cw, uint4* __restrict__ frag) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= 9 * 2 * 64) return;
+  const ConvArgs a{nullptr, nullptr, cw.w[blockIdx.y], cw.ci_n[blockIdx.y], kCC, 1};
+  const int lane = i & 63, ks = (i >> 6) & 1, tap = i >> 7;
+  const int cin = 16 * ks + 8 * (lane >> 5), cout = lane & 31;
+  uint32_t part[3][4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+  for (int e = 0; e < 4; ++e) {
+    uint32_t q[3];
+    split_pair(conv_w(a, cin + 2 * e, cout, tap / 3, tap % 3), conv_w(a, cin + 2 * e + 1, cout, tap / 3, tap % 3), q);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) acc[r][h] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float bf[8][2], bn[8][2];
-#pragma unroll
-  for (int s = 0; s < 8; ++s)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) bf[s][h] = frag[(s * 2 + h) * 64 + lane];
-#pragma unroll
-  for (int tap = 0; tap < 9; ++tap) {
-    const int ky = tap / 3, kx = tap % 3;
-    // the next tap's fragments are in flight while this tap's MFMAs run
-    const int tn = tap < 8 ? tap + 1 : tap;
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) bn[s][h] = frag[((tn * 8 + s) * 2 + h) * 64 + lane];
-    float av[4][8];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int py = wave * 4 + r;
-      const float* src = &s_in[((py + ky) * kHalo + li + kx) * kLS + 8 * lk];
-      const float4 a0 = *reinterpret_cast<const float4*>(src);
-      const float4 a1 = *reinterpret_cast<const float4*>(src + 4);
-      av[r][0] = a0.x; av[r][1] = a0.y; av[r][2] = a0.z; av[r][3] = a0.w;
-      av[r][4] = a1.x; av[r][5] = a1.y; av[r][6] = a1.z; av[r][7] = a1.w;
-    }
-    // eight independent accumulators between two MFMAs on the same one
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        acc[r][0] = mfma4(av[r][s], bf[s][0], acc[r][0]);
-        acc[r][1] = mfma4(av[r][s], bf[s][1], acc[r][1]);
-      }
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) bf[s][h] = bn[s][h];
+    for (int p = 0; p < 3; ++p) part[p][e] = q[p];
   }
-  // D[i][j]: pixel column 4 lk + e of the row, output channel 16 h + li
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int y = ty0 + wave * 4 + r;
-    if (y >= a.H) continue;
+  for (int p = 0; p < 3; ++p)
+    frag[blockIdx.y * kSplitFrag + ((tap * 2 + ks) * 3 + p) * 64 + lane] =
+        make_uint4(part[p][0], part[p][1], part[p][2], part[p][3]);
+}
+
+// Forward convolution (FP32 matrix instructions).  Persistent workgroups of eight wavefronts, one
+// workgroup per compute unit, compute 16 x 16-pixel tiles from their 18 x 18 input halo in LDS; a
+// wavefront owns 2 pixel rows.  In an MFMA the A operand is 16 output channels x 4 input channels (the
+// weights, which stay in LDS), the B operand 4 input channels x 16 pixels; the contraction order
+// inside a tap is permuted so that a lane's eight B values of a tap are eight consecutive channels of
+// one pixel (two 16-byte LDS reads), with A laid out to match, and a lane ends up with runs of four
+// output channels of one pixel.  The halo is double-buffered, so that one workgroup's matrix work
+// overlaps its own loads: three independent workgroups per compute unit, each staging, contracting
+// and storing in step with the others, left the matrix cores idle 43 % of the time.
+constexpr int kConvBlock = 512;
+constexpr int kHaloVec = kHalo * kHalo * 8;                                  // 16-byte pieces of a halo
+constexpr int kHaloPer = (kHaloVec + kConvBlock - 1) / kConvBlock;           // per thread
+
+// A thread's pieces of a halo: their place in the window and in memory, the same for every tile.
+struct HaloLoad {
+  int off[kHaloPer], row[kHaloPer], col[kHaloPer];
+  __device__ __forceinline__ explicit HaloLoad(int W) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int x = tx0 + 4 * lk + e;
-      if (x >= a.W) continue;
-      const int64_t base = ((int64_t)y * a.W + x) * kCC;
+    for (int j = 0; j < kHaloPer; ++j) {
+      const int i = threadIdx.x + kConvBlock * j, pix = i >> 3;
+      row[j] = i < kHaloVec ? pix / kHalo : (1 << 30);   // past every image
+      col[j] = pix % kHalo;
+      off[j] = (pix / kHalo * W + col[j]) * 128 + 16 * (i & 7);
+    }
+  }
+  __device__ __forceinline__ void load(float4 (&v)[kHaloPer], const ConvArgs& a, int tile, int tiles_x) const {
+    const int ty0 = tile / tiles_x * kTS - 1, tx0 = tile % tiles_x * kTS - 1;
+    const Window win(a.in, a.W, ty0, kHalo);
+#pragma unroll
+    for (int j = 0; j < kHaloPer; ++j)
+      v[j] = win.load((unsigned)(ty0 + row[j]) < (unsigned)a.H && (unsigned)(tx0 + col[j]) < (unsigned)a.W,
+                      off[j] + tx0 * 128);
+  }
+};
+
+__global__ __launch_bounds__(kConvBlock) void k_conv3x3(ConvArgs a, const float4* __restrict__ frag) {
+  __shared__ float4 s_in[2][kHalo * kHalo * kLS / 4];
+  __shared__ float4 s_w[kFrag / 4];
+  const int tiles_x = (a.W + kTS - 1) / kTS, n_tiles = tiles_x * ((a.H + kTS - 1) / kTS);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int li = lane & 15, lk = lane >> 4;
+  const HaloLoad halo(a.W);
+  float4 v[kHaloPer];
+  auto load = [&](int tile) { halo.load(v, a, tile < n_tiles ? tile : n_tiles - 1, tiles_x); };
+  auto stage = [&](float4* dst) {
+#pragma unroll
+    for (int j = 0; j < kHaloPer; ++j) {
+      const int i = tid + kConvBlock * j;
+      if (i < kHaloVec) dst[(i >> 3) * (kLS / 4) + (i & 7)] = v[j];
+    }
+  };
+  load(blockIdx.x);   // the grid has at most n_tiles workgroups
+  for (int i = tid; i < kFrag / 4; i += kConvBlock) s_w[i] = frag[i];
+  float bias[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bias[h][e] = a.bias[16 * h + 4 * lk + e];
+  stage(s_in[0]);
+  load(blockIdx.x + gridDim.x);
+  int buf = 0;
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x, buf ^= 1) {
+    const int x = tile % tiles_x * kTS + li, y0 = tile / tiles_x * kTS + wave * 2;
+    __syncthreads();   // this tile is staged, and the other buffer's readers are done
+    float4 add[2][2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int co = 16 * h + li;
-        float v = acc[r][h][e];
-        if (a.bias && co < (a.transpose ? a.ci_n : a.co_n)) v += a.bias[co];
-        if (a.addend) v += a.addend[base + co];
-        if (a.relu) v = fmaxf(v, 0.f);
-        if (a.mask) v = a.mask[base + co] > 0.f ? v : 0.f;
-        a.out[base + co] = v;
+        const int64_t at = y0 + r < a.H && x < a.W ? (int64_t)(y0 + r) * a.W + x : 0;
+        add[r][h] = a.addend ? reinterpret_cast<const float4*>(a.addend)[at * 8 + 4 * h + lk]
+                             : make_float4(0.f, 0.f, 0.f, 0.f);
       }
+    floatx4 acc[2][2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc[r][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      float wf[2][8], xf[2][8];
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float4 w4 = s_w[(tap * 4 + 2 * r + q) * 64 + lane];
+          const float4 x4 = s_in[buf][((wave * 2 + r + tap / 3) * kHalo + li + tap % 3) * (kLS / 4) + 2 * lk + q];
+          wf[r][4 * q] = w4.x; wf[r][4 * q + 1] = w4.y; wf[r][4 * q + 2] = w4.z; wf[r][4 * q + 3] = w4.w;
+          xf[r][4 * q] = x4.x; xf[r][4 * q + 1] = x4.y; xf[r][4 * q + 2] = x4.z; xf[r][4 * q + 3] = x4.w;
+        }
+      // four independent accumulators between two MFMAs on the same one
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) acc[r][h] = mfma4(wf[h][s], xf[r][s], acc[r][h]);
+    }
+    // D[i][j]: output channel 16 h + 4 lk + e, pixel column li of the row
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const bool ok = y0 + r < a.H && x < a.W;
+      const int64_t at = (int64_t)(y0 + r) * a.W + x;
+      uint32_t on = 0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float ad[4] = {add[r][h].x, add[r][h].y, add[r][h].z, add[r][h].w};
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          o[e] = acc[r][h][e] + bias[h][e];
+          if (a.addend) o[e] += ad[e];
+          o[e] = fmaxf(o[e], 0.f);
+          on |= o[e] > 0.f ? 1u << (16 * h + e) : 0u;
+        }
+        if (ok) reinterpret_cast<float4*>(a.out)[at * 8 + 4 * h + lk] = make_float4(o[0], o[1], o[2], o[3]);
+      }
+      if (a.bits_out) {   // the ReLU's signs for the adjoint: the four lanes of a pixel together
+        on <<= 4 * lk;
+        on |= (uint32_t)__shfl_xor((int)on, 16, 64);
+        on |= (uint32_t)__shfl_xor((int)on, 32, 64);
+        if (ok && lk == 0) a.bits_out[at] = on;
+      }
+    }
+    if (tile + (int)gridDim.x < n_tiles) {   // uniform
+      stage(s_in[buf ^ 1]);
+      load(tile + 2 * gridDim.x);
     }
   }
 }
 
-__global__ __launch_bounds__(256) void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy,
-                                                        int H, int W, float* __restrict__ partial) {
-  __shared__ __align__(16) float s_x[(kWTH + 2) * kHalo * kLS];
-  __shared__ __align__(16) float s_dy[kWTH * kTS * kLS];
-  __shared__ float s_b[8][kCC];
-  const int tiles_x = (W + kTS - 1) / kTS, tiles_y = (H + kWTH - 1) / kWTH;
-  const int n_tiles = tiles_x * tiles_y;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int li = lane & 15, lk = lane >> 4;
-  floatx4 acc[9];
+// One output of a convolution in plain FP32 from global memory.
+__device__ __forceinline__ float conv_plain(const ConvArgs& a, int y, int x, int co) {
+  float s = 0.f;
+  for (int tap = 0; tap < 9; ++tap) {
+    const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
+    if (yy < 0 || yy >= a.H || xx < 0 || xx >= a.W) continue;
+    for (int c = 0; c < kCC; ++c)
+      s = fmaf(a.in[((int64_t)yy * a.W + xx) * kCC + c], conv_w(a, c, co, tap / 3, tap % 3), s);
+  }
+  return s;
+}
+
+// Either convolution for images wider than kMaxWidth: a thread per output, 32 channels of a pixel in
+// consecutive lanes.
+__global__ __launch_bounds__(256) void k_conv_plain(ConvArgs a) {
+  const int64_t n = (int64_t)a.W * a.H * kCC;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {   // n % 32 == 0
+    const int64_t at = i / kCC;
+    const int c = (int)(i % kCC);
+    float v = conv_plain(a, (int)(at / a.W), (int)(at % a.W), c);
+    if (!a.transpose) v += a.bias[c];
+    if (a.addend) v += a.addend[i];
+    if (!a.transpose) v = fmaxf(v, 0.f);
+    if (a.mask) v = (a.mask[at] >> c) & 1u ? v : 0.f;
+    a.out[i] = v;
+    const uint64_t on = __ballot(v > 0.f);
+    if (a.bits_out && c == 0) a.bits_out[at] = (uint32_t)(on >> (threadIdx.x & 32));
+  }
+}
+
+// Input-gradient convolution on the bf16 matrix cores (split operands, see above).  Persistent
+// workgroups of eight wavefronts, one workgroup per compute unit, compute 16 x 16-pixel tiles; a
+// wavefront owns 2 pixel rows, and an MFMA contracts 16 channels for 32 output channels (operand A,
+// the weights) x 32 pixels (operand B).  The split weights (55 KB) stay in LDS: fetched per tap and
+// wavefront they cost as many bytes through the L1 as the matrix cores could use, and held in
+// registers (216) they leave one wavefront per SIMD and nothing to hide the LDS latency.  The 18 x 18
+// halo is split while it is staged (each value once, not once per tap), three 64-byte parts per pixel
+// in LDS rows of 13 x 16 bytes (an odd count, so that 16 pixels read by one instruction spread over
+// all banks).  The next two tiles' loads are in flight while this one is contracted (one tile's 41 KB
+// per compute unit do not keep HBM busy).
+constexpr int kSplitRow = 13;     // uint4 per pixel in LDS: 3 parts x 4, and one of padding
+
+__global__ __launch_bounds__(kConvBlock) void k_conv3x3_bwd(ConvArgs a, const uint4* __restrict__ frag) {
+  __shared__ uint4 s_in[kHalo * kHalo * kSplitRow];
+  __shared__ uint4 s_w[kSplitFrag];
+  const int tiles_x = (a.W + kTS - 1) / kTS, n_tiles = tiles_x * ((a.H + kTS - 1) / kTS);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int px = lane & 15, pr = (lane >> 4) & 1, kh = lane >> 5;
+  // after the swap below a lane holds, of the pixels (px, row 0 and 1 of the wavefront), the 16-byte
+  // pieces c4 and c4 + 4: 64 contiguous bytes per 4 lanes (16-byte pieces of other lines would cost
+  // twice the bytes written to HBM)
+  const int c4 = 2 * pr + kh;
+  const HaloLoad halo(a.W);
+  float4 va[kHaloPer], vb[kHaloPer];   // the next two tiles' halos
+  // unconditional: no branch around the loads
+  auto load = [&](float4 (&v)[kHaloPer], int tile) { halo.load(v, a, tile < n_tiles ? tile : n_tiles - 1, tiles_x); };
+  float bad = 0.f;   // not a number once an output is not finite
+  load(va, blockIdx.x);
+  load(vb, blockIdx.x + gridDim.x);
+  for (int i = tid; i < kSplitFrag; i += kConvBlock) s_w[i] = frag[i];
+  auto tile_step = [&](float4 (&v)[kHaloPer], int tile) {
+    const int ty0 = tile / tiles_x * kTS, tx0 = tile % tiles_x * kTS;
+    __syncthreads();   // the previous tile's readers are done
 #pragma unroll
-  for (int m = 0; m < 9; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float accb = 0.f;
-  const int bco = threadIdx.x & 31, bg = threadIdx.x >> 5;
-  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const int tx0 = (tile % tiles_x) * kTS, ty0 = (tile / tiles_x) * kWTH;
-    __syncthreads();   // the previous tile's LDS reads are done
-    stage_window<kWTH + 2, kHalo>(x, H, W, ty0 - 1, tx0 - 1, s_x);
-    stage_window<kWTH, kTS>(dy, H, W, ty0, tx0, s_dy);
+    for (int j = 0; j < kHaloPer; ++j) {
+      const int i = tid + kConvBlock * j, pix = i >> 3, q = i & 7;
+      if (i >= kHaloVec) break;
+      uint32_t lo[3], hi[3];
+      split_pair(v[j].x, v[j].y, lo);
+      split_pair(v[j].z, v[j].w, hi);
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        reinterpret_cast<uint2*>(&s_in[pix * kSplitRow + 4 * p])[q] = make_uint2(lo[p], hi[p]);
+    }
     __syncthreads();
-    for (int q = bg; q < kWTH * kTS; q += 8) accb += s_dy[q * kLS + bco];
-    // nine independent accumulators (output blocks: tap, input-channel half, output half)
-    // between two MFMAs on the same one
-#pragma unroll 2
-    for (int s = 0; s < kWTH * kTS / 4; ++s) {
-      const int pix = 4 * s + lk;
-      const int py = pix >> 4, px = pix & 15;
-      const float bv0 = s_dy[pix * kLS + li], bv1 = s_dy[pix * kLS + 16 + li];
+    // the epilogue's inputs first (they are needed first), then the halo two tiles ahead
+    const int x = tx0 + px, y0 = ty0 + wave * 2;
+    float4 add[2][2];
+    uint32_t msk[2];
 #pragma unroll
-      for (int m = 0; m < 9; ++m) {
-        const int t = wave + 4 * m;
-        const int tap = t >> 2, ch = (t >> 1) & 1, oh = t & 1;
-        const int ky = tap / 3, kx = tap % 3;
-        const float av = s_x[((py + ky) * kHalo + px + kx) * kLS + 16 * ch + li];
-        acc[m] = mfma4(av, oh ? bv1 : bv0, acc[m]);
+    for (int r = 0; r < 2; ++r) {
+      const bool ok = y0 + r < a.H && x < a.W;
+      const int64_t at = ok ? (int64_t)(y0 + r) * a.W + x : 0;
+      msk[r] = a.mask ? a.mask[at] : ~0u;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        add[r][u] = a.addend ? reinterpret_cast<const float4*>(a.addend)[at * 8 + c4 + 4 * u]
+                             : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    load(v, tile + 2 * gridDim.x);
+    floatx16 acc[3];   // by magnitude
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = acc[2][e] = 0.f;
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      const uint4* src = &s_in[((wave * 2 + pr + tap / 3) * kHalo + px + tap % 3) * kSplitRow + kh];
+      uint4 xf[2][3], wf[2][3];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          wf[ks][p] = s_w[((tap * 2 + ks) * 3 + p) * 64 + lane];
+          xf[ks][p] = src[4 * p + 2 * ks];
+        }
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < kProd; ++i)
+          acc[prod_acc(i)] = mfma16(wf[ks][prod_a(i)], xf[ks][prod_b(i)], acc[prod_acc(i)]);
+    }
+    // D: column lane & 31 = pixel, row 8 g + 4 kh + e = channel
+    float o[2][2][4];   // [pixel row][piece][channel]
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float g0 = (acc[0][8 * u + e] + acc[1][8 * u + e]) + acc[2][8 * u + e];
+        const float g1 = (acc[0][8 * u + 4 + e] + acc[1][8 * u + 4 + e]) + acc[2][8 * u + 4 + e];
+        auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(g0), __float_as_uint(g1), false, false);
+        o[0][u][e] = __uint_as_float(r[0]);
+        o[1][u][e] = __uint_as_float(r[1]);
+      }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      if (y0 + r >= a.H || x >= a.W) continue;
+      const int64_t at = (int64_t)(y0 + r) * a.W + x;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const float ad[4] = {add[r][u].x, add[r][u].y, add[r][u].z, add[r][u].w};
+        const uint32_t m = msk[r] >> (4 * c4 + 16 * u);
+        float w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t keep = (uint32_t)((int32_t)(m << (31 - e)) >> 31);   // all ones where the bit is set
+          w[e] = __uint_as_float(__float_as_uint(o[r][u][e] + ad[e]) & keep);
+          bad = SPLAT_FMA(w[e], 0.f, bad);
+        }
+        reinterpret_cast<float4*>(a.out)[at * 8 + c4 + 4 * u] = make_float4(w[0], w[1], w[2], w[3]);
       }
     }
+  };
+  for (int tile = blockIdx.x; tile < n_tiles; tile += 2 * gridDim.x) {
+    tile_step(va, tile);
+    if (tile + (int)gridDim.x < n_tiles) tile_step(vb, tile + gridDim.x);   // uniform
   }
+  if (bad == 0.f) return;   // else the lane's own stores that are not finite, in plain FP32
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)
+    for (int i = 0; i < 16; ++i) {
+      const int y = tile / tiles_x * kTS + wave * 2 + (i >> 3), x = tile % tiles_x * kTS + px;
+      const int c = 4 * c4 + 16 * ((i >> 2) & 1) + (i & 3);
+      if (y >= a.H || x >= a.W) continue;
+      const int64_t at = (int64_t)y * a.W + x;
+      if (finite_f(a.out[at * kCC + c])) continue;   // masked outputs are zero
+      const float s = conv_plain(a, y, x, c);
+      a.out[at * kCC + c] = a.addend ? s + a.addend[at * kCC + c] : s;
+    }
+}
+
+// Weight gradient dW[tap][ci][co] = sum_p x[p + tap][ci] dy[p][co] on the bf16 matrix cores (split
+// operands, see above): persistent workgroups stage 8-row x 16-column tiles.  An MFMA contracts 16
+// pixels (2 columns x 8 rows) for 32 input x 32 output channels, so a lane needs 8 rows of one
+// channel: the staging transposes, a thread reading a column of 8 rows x 4 channels and writing each
+// channel's rows as 16 bytes.  A tap's column offset is then another 16-byte slot, and its row
+// offset a funnel shift of the ten staged rows (registers), so each x fragment serves three taps.
+// Twelve wavefronts, three per SIMD: three column offsets x four quarters of the columns, three
+// 32 x 32 blocks each.  The tile is double-buffered: the next one's loads are in flight while this one
+// is contracted, and are split into the other buffer before the one barrier per tile.  The quarters
+// are added at the end, and a second kernel adds the workgroups' partial sums in a fixed order.
+constexpr int kWgradBlock = 768;
+constexpr int kXCol = 19;   // uint4 slots of a channel's 18 halo columns (odd: spreads over banks)
+constexpr int kDyCol = 17;  // the same for its 16 columns
+
+struct WgradSmem {
+  uint4 x[3][kCC][kXCol];        // rows 0-7 of the ten halo rows, two per word
+  uint32_t x_tail[3][kCC][kXCol];  // rows 8, 9
+  uint4 dy[3][kCC][kDyCol];
+};
+
+// splits NR rows of four channels; put(part, channel, words) stores a channel's rows, two per word
+template <int NR, typename Put>
+__device__ __forceinline__ void split_rows(const float4 (&v)[NR], Put put) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    uint32_t w[3][NR / 2];
+#pragma unroll
+    for (int h = 0; h < NR / 2; ++h) {
+      const float4 u0 = v[2 * h], u1 = v[2 * h + 1];
+      uint32_t q[3];
+      split_pair(c == 0 ? u0.x : c == 1 ? u0.y : c == 2 ? u0.z : u0.w,
+                 c == 0 ? u1.x : c == 1 ? u1.y : c == 2 ? u1.z : u1.w, q);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) w[p][h] = q[p];
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) put(p, c, w[p]);
+  }
+}
+
+// The workgroup's partial sums that are not finite, once more in plain FP32 (values that do not split
+// end up there: a part of theirs is not a number).  Images wider than kMaxWidth take it for all.
+__device__ __forceinline__ void wgrad_plain(const float* __restrict__ x, const float* __restrict__ dy, int H, int W,
+                                            float* __restrict__ dst) {
+  const int tiles_x = (W + kTS - 1) / kTS, tiles_y = (H + kWTH - 1) / kWTH;
+  for (int i = threadIdx.x; i < 9 * kCC * kCC; i += kWgradBlock) {
+    if (finite_f(dst[i])) continue;
+    const int tap = i / (kCC * kCC), ci = (i / kCC) % kCC, co = i % kCC;
+    float s = 0.f;
+    for (int tile = blockIdx.x; tile < tiles_x * tiles_y; tile += gridDim.x)
+      for (int p = 0; p < kWTH * kTS; ++p) {
+        const int yy = tile / tiles_x * kWTH + p / kTS, xx = tile % tiles_x * kTS + p % kTS;
+        const int ys = yy + tap / 3 - 1, xs = xx + tap % 3 - 1;
+        if (yy >= H || xx >= W || ys < 0 || ys >= H || xs < 0 || xs >= W) continue;
+        s = fmaf(x[((int64_t)ys * W + xs) * kCC + ci], dy[((int64_t)yy * W + xx) * kCC + co], s);
+      }
+    dst[i] = s;
+  }
+}
+
+__global__ __launch_bounds__(kWgradBlock)
+void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, int H, int W, float* __restrict__ partial) {
+  __shared__ union {
+    WgradSmem t[2];
+    float red[9 * kCC * kCC];
+    float b[16 * 8][2][4];
+  } sm;
+  const int tiles_x = (W + kTS - 1) / kTS, tiles_y = (H + kWTH - 1) / kWTH;
+  const int n_tiles = tiles_x * tiles_y;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int ch = lane & 31, kh = lane >> 5;
+  const int kx = wave % 3, quarter = wave / 3;
   float* dst = partial + (int64_t)blockIdx.x * kWOut;
+  if (W > kMaxWidth) {   // uniform
+    for (int i = tid; i < 9 * kCC * kCC; i += kWgradBlock) dst[i] = INFINITY;
+    wgrad_plain(x, dy, H, W, dst);
+    if (tid < kCC) {
+      float s = 0.f;
+      for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)
+        for (int p = 0; p < kWTH * kTS; ++p) {
+          const int yy = tile / tiles_x * kWTH + p / kTS, xx = tile % tiles_x * kTS + p % kTS;
+          if (yy < H && xx < W) s += dy[((int64_t)yy * W + xx) * kCC + tid];
+        }
+      dst[9 * kCC * kCC + tid] = s;
+    }
+    return;
+  }
+  floatx16 acc[3];
 #pragma unroll
-  for (int m = 0; m < 9; ++m) {
-    const int t = wave + 4 * m;
-    const int tap = t >> 2, ch = (t >> 1) & 1, oh = t & 1;
+  for (int m = 0; m < 3; ++m)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int ci = 16 * ch + 4 * lk + e, co = 16 * oh + li;
-      dst[(tap * kCC + ci) * kCC + co] = acc[m][e];
+    for (int e = 0; e < 16; ++e) acc[m][e] = 0.f;
+  float accb[4] = {0.f, 0.f, 0.f, 0.f};
+  // the odd workgroups contract -dy and negate their sums (the instruction's rounding bias cancels)
+  const uint32_t sign = (blockIdx.x & 1) ? 0x80000000u : 0u;
+  // staging tasks of (column, four channels, four rows): threads 0-255 the 16 dy columns, threads
+  // 256-543 the 18 x columns (rows 0-7); threads 544-687 rows 8, 9 of the x columns
+  const int q = tid & 7;
+  const bool is_dy = tid < 256, is_tail = tid >= 544;
+  const bool is_dy_wave = __builtin_amdgcn_readfirstlane(tid) < 256;   // the same, as a scalar
+  const int part = tid < 544 ? (tid >> 3) & 1 : 2;   // rows 4 part ...
+  const int col = is_dy ? tid >> 4 : is_tail ? (tid - 544) >> 3 : (tid - 256) >> 4;
+  const int r0 = 4 * part + (is_dy ? 1 : 0);   // from the row above the tile
+  const int off = (r0 * W + (is_dy ? col : col - 1)) * 128 + 16 * q;
+  const int rows = tid < 544 ? 4 : tid < 688 ? 2 : 0;
+  float4 v[4];
+  auto load = [&](int tile) {   // in flight while the previous tile is contracted
+    tile = tile < n_tiles ? tile : n_tiles - 1;   // unconditional: no branch around the loads
+    const int ty0 = tile / tiles_x * kWTH - 1, tx0 = tile % tiles_x * kTS;
+    const bool in_x = (unsigned)(tx0 + (is_dy ? col : col - 1)) < (unsigned)W;
+    const Window win(is_dy_wave ? dy : x, W, ty0, kWTH + 2);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      v[r] = win.load(in_x && r < rows && (unsigned)(ty0 + r0 + r) < (unsigned)H, off + (r * W + tx0) * 128);
+  };
+  auto stage = [&](WgradSmem& t) {   // splits the loaded values into a buffer
+    if (is_dy) {   // uniform over the wavefront
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        accb[0] += v[r].x;
+        accb[1] += v[r].y;
+        accb[2] += v[r].z;
+        accb[3] += v[r].w;
+        v[r].x = __uint_as_float(__float_as_uint(v[r].x) ^ sign);
+        v[r].y = __uint_as_float(__float_as_uint(v[r].y) ^ sign);
+        v[r].z = __uint_as_float(__float_as_uint(v[r].z) ^ sign);
+        v[r].w = __uint_as_float(__float_as_uint(v[r].w) ^ sign);
+      }
+    }
+    if (is_tail) {
+      if (rows)
+        split_rows<2>({v[0], v[1]}, [&](int p, int c, const uint32_t (&w)[1]) { t.x_tail[p][4 * q + c][col] = w[0]; });
+    } else {
+      split_rows<4>(v, [&](int p, int c, const uint32_t (&w)[2]) {
+        uint4* dst = is_dy ? &t.dy[p][4 * q + c][col] : &t.x[p][4 * q + c][col];
+        reinterpret_cast<uint2*>(dst)[part] = make_uint2(w[0], w[1]);
+      });
+    }
+  };
+  load(blockIdx.x);   // the grid has at most n_tiles workgroups
+  stage(sm.t[0]);
+  load(blockIdx.x + gridDim.x);
+  int buf = 0;
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x, buf ^= 1) {
+    __syncthreads();
+    const WgradSmem& t = sm.t[buf];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {   // the wavefront's two pairs of columns
+      const int cx = 4 * quarter + 2 * k + kh;
+      uint4 g[3], f[3][3];   // f: [row offset][part]
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        g[p] = t.dy[p][ch][cx];
+        const uint4 u = t.x[p][ch][cx + kx];
+        const uint32_t w = t.x_tail[p][ch][cx + kx];
+        f[0][p] = u;
+        f[1][p] = make_uint4(__builtin_amdgcn_alignbit(u.y, u.x, 16), __builtin_amdgcn_alignbit(u.z, u.y, 16),
+                             __builtin_amdgcn_alignbit(u.w, u.z, 16), __builtin_amdgcn_alignbit(w, u.w, 16));
+        f[2][p] = make_uint4(u.y, u.z, u.w, w);
+      }
+#pragma unroll
+      for (int i = 0; i < kProd; ++i)
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) acc[ky] = mfma16(f[ky][prod_a(i)], g[prod_b(i)], acc[ky]);
+    }
+    // the other buffer was last read before this iteration's barrier
+    if (tile + (int)gridDim.x < n_tiles) {   // uniform
+      stage(sm.t[buf ^ 1]);
+      load(tile + 2 * gridDim.x);
     }
   }
-  s_b[bg][bco] = accb;
-  __syncthreads();
-  if (threadIdx.x < kCC) {
-    float s = 0.f;
-    for (int g = 0; g < 8; ++g) s += s_b[g][threadIdx.x];
-    dst[9 * kCC * kCC + threadIdx.x] = s;
+  for (int w = 0; w < 4; ++w) {   // the column quarters, in order
+    __syncthreads();
+    if (quarter == w) {
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int i = ((3 * m + kx) * kCC + 8 * (e >> 2) + 4 * kh + (e & 3)) * kCC + ch;
+          sm.red[i] = w == 0 ? acc[m][e] : sm.red[i] + acc[m][e];
+        }
+    }
   }
+  __syncthreads();
+  float bad = 0.f;   // not a number once a sum is not finite
+  for (int i = tid; i < 9 * kCC * kCC; i += kWgradBlock) {
+    const float s = __uint_as_float(__float_as_uint(sm.red[i]) ^ sign);
+    bad = SPLAT_FMA(s, 0.f, bad);
+    dst[i] = s;
+  }
+  __syncthreads();
+  if (is_dy) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sm.b[col * 8 + q][part][c] = accb[c];
+  }
+  __syncthreads();
+  if (tid < kCC) {   // channel 4 q + c: the 16 dy columns in order
+    float s = 0.f;
+    for (int c = 0; c < 16; ++c) s += sm.b[c * 8 + (tid >> 2)][0][tid & 3] + sm.b[c * 8 + (tid >> 2)][1][tid & 3];
+    dst[9 * kCC * kCC + tid] = s;
+  }
+  if (bad != 0.f) wgrad_plain(x, dy, H, W, dst);   // its loop visits the same entries per thread
 }
 
 // dW (OIHW, +=) and db (+=) of one convolution from the column sums of the partials
@@ -502,14 +928,16 @@ __global__ __launch_bounds__(kCnnBlock) void k_cnn_head_bwd(const float* __restr
 struct CnnWs {
   float* act[6];   // x0, h0, r1, h1, r2, h2
   float* g[3];     // gradient buffers
-  float* frag;     // B fragments of the convolution being launched
+  uint32_t* bits[4];   // the signs of act[1 .. 4], a bit per channel
+  float* frag;     // A fragments of the five forward convolutions
+  uint4* sfrag;    // split A fragments of the five input-gradient convolutions
   float* partial;  // partial sums
   size_t bytes;
 };
 
 inline int wgrad_blocks(int W, int H) {
   const int tiles = ((W + kTS - 1) / kTS) * ((H + kWTH - 1) / kWTH);
-  return tiles < 768 ? tiles : 768;
+  return tiles < 256 ? tiles : 256;   // one workgroup per compute unit
 }
 inline int head_blocks(int64_t n) {
   const int64_t b = (n + kCnnBlock - 1) / kCnnBlock;
@@ -527,8 +955,11 @@ inline CnnWs carve_cnn(void* base, int W, int H) {
   auto at = [&](size_t o) { return b ? (float*)(b + o) : nullptr; };
   for (int i = 0; i < 6; ++i, off += act) w.act[i] = at(off);
   for (int i = 0; i < 3; ++i, off += act) w.g[i] = at(off);
+  for (int i = 0; i < 4; ++i, off += ((size_t)n * 4 + 255) / 256 * 256) w.bits[i] = (uint32_t*)at(off);
   w.frag = at(off);
-  off += (size_t)kFrag * sizeof(float);
+  off += (size_t)kConvs * kFrag * sizeof(float);
+  w.sfrag = (uint4*)at(off);
+  off += (size_t)kConvs * kSplitFrag * sizeof(uint4);
   size_t part = (size_t)wgrad_blocks(W, H) * kWOut;
   const size_t hp = (size_t)head_blocks(n) * kHeadOut;
   const size_t ep = (size_t)input_bwd_blocks(n) * 8;
@@ -561,20 +992,49 @@ static CnnGeo cnn_geo(const SplatCamera* cam) {
   return g;
 }
 
-static hipError_t conv(const float* in, float* out, const float* w, int ci_n, int co_n, int transpose,
-                       const float* bias, const float* addend, const float* mask, int relu, int W, int H, float* frag,
-                       hipStream_t s) {
-  ConvArgs a{in, out, w, ci_n, co_n, transpose, bias, addend, mask, relu, H, W};
-  const int tiles = ((W + kTS - 1) / kTS) * ((H + kTS - 1) / kTS);
-  hipLaunchKernelGGL(k_conv_frag, dim3((unsigned)(kFrag / 256)), dim3(256), 0, s, a, frag);
-  hipLaunchKernelGGL(k_conv3x3, dim3((unsigned)tiles), dim3(256), 0, s, a, (const float*)frag);
+// one persistent workgroup per compute unit
+static unsigned conv_grid(int W, int H) {
+  const int64_t tiles = (int64_t)((W + kTS - 1) / kTS) * ((H + kTS - 1) / kTS);
+  return (unsigned)(tiles < 256 ? tiles : 256);
+}
+
+static ConvWeights conv_weights(const SplatCameraCNN* cnn, int cin) {
+  ConvWeights cw;
+  for (int k = 0; k < kConvs; ++k) {
+    cw.w[k] = k == 0 ? cnn->w_in : cnn->w_block[k - 1];
+    cw.ci_n[k] = k == 0 ? cin : kCC;
+  }
+  return cw;
+}
+
+// forward convolution k (0: the stem, 1-4: the blocks'), ReLU after the optional addend
+static hipError_t conv(int k, const float* in, float* out, const ConvWeights& cw, const float* bias, const float* addend,
+                       int W, int H, const CnnWs& w, hipStream_t s) {
+  ConvArgs a{in, out, cw.w[k], cw.ci_n[k], kCC, 0, bias, addend, k < 4 ? w.bits[k] : nullptr, nullptr, H, W};
+  if (W > kMaxWidth)
+    hipLaunchKernelGGL(k_conv_plain, dim3(4096), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_conv3x3, dim3(conv_grid(W, H)), dim3(kConvBlock), 0, s, a,
+                       (const float4*)(w.frag + (size_t)k * kFrag));
+  return hipGetLastError();
+}
+
+// its input gradient: (addend + conv^T(in)) where mask > 0
+static hipError_t conv_bwd(int k, const float* in, float* out, const ConvWeights& cw, const float* addend,
+                           const uint32_t* mask, int W, int H, const CnnWs& w, hipStream_t s) {
+  ConvArgs a{in, out, cw.w[k], cw.ci_n[k], kCC, 1, nullptr, addend, nullptr, mask, H, W};
+  if (W > kMaxWidth)
+    hipLaunchKernelGGL(k_conv_plain, dim3(4096), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_conv3x3_bwd, dim3(conv_grid(W, H)), dim3(kConvBlock), 0, s, a,
+                       (const uint4*)(w.sfrag + (size_t)k * kSplitFrag));
   return hipGetLastError();
 }
 
 static hipError_t wgrad(const float* x, const float* dy, int ci_n, int co_n, float* dw, float* db, float* partial, int W,
                         int H, hipStream_t s) {
   const int nb = wgrad_blocks(W, H);
-  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((unsigned)nb), dim3(256), 0, s, x, dy, H, W, partial);
+  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((unsigned)nb), dim3(kWgradBlock), 0, s, x, dy, H, W, partial);
   launch_column_sums((const float*)partial, kWOut, nb, kWOut, ConvGradStore{dw, db, ci_n, co_n}, s);
   return hipGetLastError();
 }
@@ -604,14 +1064,14 @@ int splat_camera_decode(const SplatCamera* cam, const float* feat, const SplatCa
   const int vec = (((uintptr_t)feat & 15) == 0 && ((C | cnn->n_feat) & 3) == 0) ? 1 : 0;
   hipLaunchKernelGGL(k_cnn_input, dim3((unsigned)div_up(8 * n, 256)), dim3(256), 0, s, feat, C, cnn->n_feat,
                      cnn->n_embed, cnn->embed, cnn_geo(cam), vec, w.act[0]);
-  hipError_t e = conv(w.act[0], w.act[1], cnn->w_in, cin, kCC, 0, cnn->b_in, nullptr, nullptr, 1, W, H, w.frag, s);
+  const ConvWeights cw = conv_weights(cnn, cin);
+  hipLaunchKernelGGL(k_conv_frag, dim3(kFrag / 256, kConvs), dim3(256), 0, s, cw, w.frag);
+  hipError_t e = conv(0, w.act[0], w.act[1], cw, cnn->b_in, nullptr, W, H, w, s);
   for (int k = 0; k < 2 && e == hipSuccess; ++k) {
     float* hin = w.act[1 + 2 * k];
-    e = conv(hin, w.act[2 + 2 * k], cnn->w_block[2 * k], kCC, kCC, 0, cnn->b_block[2 * k], nullptr, nullptr, 1, W, H,
-             w.frag, s);
+    e = conv(1 + 2 * k, hin, w.act[2 + 2 * k], cw, cnn->b_block[2 * k], nullptr, W, H, w, s);
     if (e == hipSuccess)
-      e = conv(w.act[2 + 2 * k], w.act[3 + 2 * k], cnn->w_block[2 * k + 1], kCC, kCC, 0, cnn->b_block[2 * k + 1], hin,
-               nullptr, 1, W, H, w.frag, s);
+      e = conv(2 + 2 * k, w.act[2 + 2 * k], w.act[3 + 2 * k], cw, cnn->b_block[2 * k + 1], hin, W, H, w, s);
   }
   if (e != hipSuccess) return SPLAT_ERR_DEVICE;
   hipLaunchKernelGGL(k_cnn_head, dim3((unsigned)div_up(n, 256)), dim3(256), 0, s, (const float*)w.act[5], feat, C,
@@ -632,6 +1092,8 @@ int splat_camera_decode_bwd(const SplatCamera* cam, const float* feat, const Spl
   const int cin = cnn->n_feat + 3 + cnn->n_embed;
   float *x0 = w.act[0], *h0 = w.act[1], *r1 = w.act[2], *h1 = w.act[3], *r2 = w.act[4], *h2 = w.act[5];
   float *ga = w.g[0], *gb = w.g[1], *gc = w.g[2];
+  const ConvWeights cw = conv_weights(cnn, cin);
+  hipLaunchKernelGGL(k_conv_split_frag, dim3((9 * 2 * 64 + 255) / 256, kConvs), dim3(256), 0, s, cw, w.sfrag);
   // head: dpre2 -> ga
   const int hb = head_blocks(n);
   hipLaunchKernelGGL(k_cnn_head_bwd, dim3((unsigned)hb), dim3(kCnnBlock), 0, s, (const float*)h2, feat, C, cnn->w_out,
@@ -650,11 +1112,11 @@ int splat_camera_decode_bwd(const SplatCamera* cam, const float* feat, const Spl
     // conv_k2: its input r_k, output gradient dpre_k
     e = wgrad(r, dp, kCC, kCC, d_cnn->w_block[2 * k + 1], d_cnn->b_block[2 * k + 1], w.partial, W, H, s);
     if (e == hipSuccess)   // du_k = conv_k2^T(dpre_k) * [r_k > 0]
-      e = conv(dp, du, cnn->w_block[2 * k + 1], kCC, kCC, 1, nullptr, nullptr, r, 0, W, H, w.frag, s);
+      e = conv_bwd(2 + 2 * k, dp, du, cw, nullptr, w.bits[1 + 2 * k], W, H, w, s);
     if (e == hipSuccess)   // conv_k1: input h_{k-1}, output gradient du_k
       e = wgrad(hin, du, kCC, kCC, d_cnn->w_block[2 * k], d_cnn->b_block[2 * k], w.partial, W, H, s);
     if (e == hipSuccess)   // dpre_{k-1} = (dpre_k + conv_k1^T(du_k)) * [h_{k-1} > 0]
-      e = conv(du, dnext, cnn->w_block[2 * k], kCC, kCC, 1, nullptr, dp, hin, 0, W, H, w.frag, s);
+      e = conv_bwd(1 + 2 * k, du, dnext, cw, dp, w.bits[2 * k], W, H, w, s);
     spare[0] = dp;
     spare[1] = du;
     dp = dnext;
@@ -666,7 +1128,7 @@ int splat_camera_decode_bwd(const SplatCamera* cam, const float* feat, const Spl
   // stem: dW_in, db_in; dx0 = conv_in^T(dpre0)
   if (e == hipSuccess) e = wgrad(x0, dp, cin, kCC, d_cnn->w_in, d_cnn->b_in, w.partial, W, H, s);
   float* dx0 = spare[0];
-  if (e == hipSuccess) e = conv(dp, dx0, cnn->w_in, cin, kCC, 1, nullptr, nullptr, nullptr, 0, W, H, w.frag, s);
+  if (e == hipSuccess) e = conv_bwd(0, dp, dx0, cw, nullptr, nullptr, W, H, w, s);
   if (e != hipSuccess) return SPLAT_ERR_DEVICE;
   const int64_t eb = input_bwd_blocks(n);
   const int vec = (((uintptr_t)d_feat & 15) == 0 && ((C | cnn->n_feat) & 3) == 0) ? 1 : 0;
