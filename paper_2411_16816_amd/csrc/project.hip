@@ -237,9 +237,14 @@ __global__ __launch_bounds__(256) void k_slot_reduce_long(const uint2* __restric
   }
 }
 
-constexpr int kGaussPerLane = 4;   // Gaussians per lane of the projection adjoint and the row sums
+// Gaussians per lane (GPL) of the projection adjoint and the row sums: four, so that the mostly
+// untouched Gaussians of a large scene cost a quarter of the wavefronts; one for scenes that would
+// leave compute units idle, where a lane's Gaussians only queue behind each other (3000 Gaussians:
+// row sums 69 us with four, see kFewGaussians).
+constexpr int kGaussPerLane = 4;
+constexpr int64_t kFewGaussians = 1 << 18;   // one per lane is at most 16 wavefronts per compute unit here
 
-// Gradient of every touched record, 64 x kGaussPerLane Gaussians per wavefront (lane l:
+// Gradient of every touched record, 64 x GPL Gaussians per wavefront (lane l:
 // Gaussians l, l + 64, ...; the flags of one sensor's records loaded together), sensors in
 // order per Gaussian: the sum of the rasteriser's rows over the record's entries (positions [entry_base, entry_base + n_tiles) of
 // the slot array, rows whose flag is set; a long record's total sits in its first row), taken
@@ -247,7 +252,7 @@ constexpr int kGaussPerLane = 4;   // Gaussians per lane of the projection adjoi
 // values) goes to g2d[rec] (added to the atomic part of split lidar tiles when `accumulate` and
 // bin_sort found such a tile, *split != 0), the channel part to the features gradient.
 // Untouched records have no gradient and are skipped here and in the projection adjoint.
-template <int CMAX>
+template <int CMAX, int GPL>
 __global__ __launch_bounds__(256) void k_slot_reduce(const DevSensor* __restrict__ sens, int count, int64_t N,
                                                      int c_total, const int32_t* __restrict__ n_tiles,
                                                      const uint8_t* __restrict__ rflag,
@@ -259,11 +264,11 @@ __global__ __launch_bounds__(256) void k_slot_reduce(const DevSensor* __restrict
   constexpr int V = kNV + CMAX;
   constexpr int SW = slot_stride(CMAX);
   const int lane = threadIdx.x & 63;
-  const int64_t i0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (64 * kGaussPerLane) + lane;
+  const int64_t i0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (64 * GPL) + lane;
   for (int k = 0; k < count; ++k) {
     uint32_t tm = 0;   // bit j: record (k, i0 + 64 j) was touched; flags loaded together
 #pragma unroll
-    for (int j = 0; j < kGaussPerLane; ++j) {
+    for (int j = 0; j < GPL; ++j) {
       const int64_t i = i0 + 64 * j;
       const int64_t ic = i < N ? i : N - 1;   // unconditional loads, in bounds
       tm |= (rflag[(int64_t)k * N + ic] != 0 && i < N) ? 1u << j : 0u;
@@ -283,19 +288,21 @@ __global__ __launch_bounds__(256) void k_slot_reduce(const DevSensor* __restrict
         for (int c = 0; c < nc; ++c) add_row<SW>(slots + (base + (int64_t)c * kChunk) * SW, acc);
       } else if (n > 0) {
         uint32_t fm = flag_mask(flags, base, n);
-        while (fm) {   // two rows in flight per iteration
-          const int j0 = __builtin_ctz(fm);
-          fm &= fm - 1;
-          const bool two = fm != 0;
-          const int j1 = two ? __builtin_ctz(fm) : j0;
-          if (two) fm &= fm - 1;
-          float r0[V], r1[V];
+        // G rows in flight per iteration, added in pairs
+        constexpr int G = GPL == 1 && CMAX <= 16 ? 4 : 2;
+        while (fm) {
+          float row[G][V];
 #pragma unroll
-          for (int v = 0; v < V; ++v) r0[v] = r1[v] = 0.f;
-          add_row<SW>(slots + (base + j0) * SW, r0);
-          add_row<SW>(slots + (base + j1) * SW, r1);
+          for (int u = 0; u < G; ++u) {
 #pragma unroll
-          for (int v = 0; v < V; ++v) acc[v] += two ? r0[v] + r1[v] : r0[v];
+            for (int v = 0; v < V; ++v) row[u][v] = 0.f;
+            if (fm) add_row<SW>(slots + (base + __builtin_ctz(fm)) * SW, row[u]);
+            fm &= fm - 1;
+          }
+#pragma unroll
+          for (int u = 0; u < G; u += 2)
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc[v] += row[u][v] + row[u + 1][v];
         }
       }
       // lidar records add to the atomic part of split tiles; camera rows are only ever written here
@@ -378,21 +385,22 @@ __device__ __forceinline__ void project_bwd_one(const DevSensor* __restrict__ se
   }
 }
 
-// Projection adjoint over the call's Gaussians.  A wavefront covers 64 x kGaussPerLane of them
+// Projection adjoint over the call's Gaussians.  A wavefront covers 64 x GPL of them
 // (lane l: Gaussians l, l + 64, ...): the gradient flags of all of them are loaded first, all
 // in flight together, and only the groups of 64 that hold a touched Gaussian run the projection
 // adjoint — most Gaussians of a scene receive no gradient, and the kernel's register use (3
 // wavefronts per SIMD) would otherwise spend most of its time launching wavefronts that only
 // test their flags.
+template <int GPL>
 __global__ __launch_bounds__(256) void k_project_bwd(const DevSensor* __restrict__ sens, int count, SplatGaussians g,
                                                      const uint8_t* __restrict__ rflag, const float* __restrict__ g2d,
                                                      SplatGrads gr) {
   const int lane = threadIdx.x & 63;
-  const int64_t i0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (64 * kGaussPerLane) + lane;
+  const int64_t i0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (64 * GPL) + lane;
   uint32_t tm = 0;   // bit j: Gaussian i0 + 64 j received a gradient in some record
   for (int k = 0; k < count; ++k) {
 #pragma unroll
-    for (int j = 0; j < kGaussPerLane; ++j) {
+    for (int j = 0; j < GPL; ++j) {
       const int64_t i = i0 + 64 * j;
       const int64_t ic = i < g.n ? i : g.n - 1;   // unconditional loads, in bounds
       const bool f = rflag[(int64_t)k * g.n + ic] != 0;
@@ -404,7 +412,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(const DevSensor* __restrict
   bool store = false;
   const int slot = want_s ? scatter_slot<6>(lane, store) : 0;
 #pragma unroll 1
-  for (int j = 0; j < kGaussPerLane; ++j) {
+  for (int j = 0; j < GPL; ++j) {
     const bool live = ((tm >> j) & 1u) != 0;
     if (__ballot(live) == 0) continue;   // uniform: nothing to add for this group
     project_bwd_one(sens, count, g, rflag, g2d, gr, i0 + 64 * j, live, want_s, slot, store);
@@ -425,12 +433,20 @@ hipError_t launch_project_bwd(const CallView& v, const SplatGaussians& g, const 
   const int cm = cmax_bucket(v.c_max);
   if (w.stride != slot_stride(cm)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)div_up(g.n, 256));
-  const dim3 grid_bwd((unsigned)div_up(g.n, 256 * kGaussPerLane));
+  const bool few = g.n <= kFewGaussians;
+  const dim3 grid_bwd((unsigned)div_up(g.n, 256 * (few ? 1 : kGaussPerLane)));
+  auto project_bwd = [&] {
+    if (few)
+      hipLaunchKernelGGL(k_project_bwd<1>, grid_bwd, dim3(256), 0, s, v.sens, v.count, g, (const uint8_t*)w.rflag,
+                         (const float*)w.g2d, gr);
+    else
+      hipLaunchKernelGGL(k_project_bwd<kGaussPerLane>, grid_bwd, dim3(256), 0, s, v.sens, v.count, g,
+                         (const uint8_t*)w.rflag, (const float*)w.g2d, gr);
+  };
   float* dfeat = v.c_max > 0 ? gr.features : nullptr;
   const int64_t n_rec = (int64_t)v.count * g.n;
   if (!w.rows) {   // every work item added its sums to g2d and the features gradient
-    hipLaunchKernelGGL(k_project_bwd, grid_bwd, dim3(256), 0, s, v.sens, v.count, g, (const uint8_t*)w.rflag,
-                       (const float*)w.g2d, gr);
+    project_bwd();
     return hipGetLastError();
   }
   if (w.long_cap != long_part_cap(n_rec, L.k_cap)) return hipErrorInvalidValue;
@@ -439,15 +455,18 @@ hipError_t launch_project_bwd(const CallView& v, const SplatGaussians& g, const 
                      (const uint8_t*)w.rflag, (const int64_t*)L.entry_base, n_rec, L.k_cap, (uint2*)w.long_list,
                      w.long_cap, w.n_long);
   const int64_t long_blocks = div_up(n_rec, 4) < 4096 ? div_up(n_rec, 4) : 4096;
+#define SR_LAUNCH(CM, GPL)                                                                                        \
+  hipLaunchKernelGGL((k_slot_reduce<CM, GPL>), grid_bwd, dim3(256), 0, s, v.sens, v.count, g.n, g.c_total,        \
+                     (const int32_t*)p.n_tiles, (const uint8_t*)w.rflag, (const int64_t*)L.entry_base,            \
+                     (const float*)w.slots, (const uint8_t*)w.flags, L.k_cap, v.has_lidar,                        \
+                     (const int32_t*)L.n_work + 2, w.g2d, dfeat)
 #define SR_CASE(CM)                                                                                               \
   case CM:                                                                                                        \
     hipLaunchKernelGGL(k_slot_reduce_long<CM>, dim3((unsigned)long_blocks), dim3(256), 0, s,                      \
                        (const uint2*)w.long_list, w.long_cap, (const int32_t*)w.n_long,                           \
                        (const int32_t*)p.n_tiles, (const int64_t*)L.entry_base, w.slots, w.flags, L.k_cap);       \
-    hipLaunchKernelGGL(k_slot_reduce<CM>, grid_bwd, dim3(256), 0, s, v.sens, v.count, g.n, g.c_total,                 \
-                       (const int32_t*)p.n_tiles, (const uint8_t*)w.rflag, (const int64_t*)L.entry_base,          \
-                       (const float*)w.slots, (const uint8_t*)w.flags, L.k_cap, v.has_lidar,                      \
-                       (const int32_t*)L.n_work + 2, w.g2d, dfeat);                                               \
+    if (few) SR_LAUNCH(CM, 1);                                                                                    \
+    else SR_LAUNCH(CM, kGaussPerLane);                                                                            \
     break;
   switch (cm) {
     SR_CASE(4)
@@ -457,8 +476,8 @@ hipError_t launch_project_bwd(const CallView& v, const SplatGaussians& g, const 
     SR_CASE(48)
   }
 #undef SR_CASE
-  hipLaunchKernelGGL(k_project_bwd, grid_bwd, dim3(256), 0, s, v.sens, v.count, g, (const uint8_t*)w.rflag,
-                     (const float*)w.g2d, gr);
+#undef SR_LAUNCH
+  project_bwd();
   return hipGetLastError();
 }
 

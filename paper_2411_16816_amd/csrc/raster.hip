@@ -14,7 +14,8 @@
 // are summed across the wavefront (reduce-scatter over permlane swaps and DPP), across the
 // workgroup in LDS, and stored as one row per (tile, Gaussian) entry at the entry's number
 // (record-major), where the projection adjoint sums each record's rows in a fixed order.  Only work
-// items of lidar tiles split over several items add their rows with global atomics.
+// items of lidar tiles split over several items add their rows with global atomics.  Calls with too
+// few items to fill the chip walk each list in segments side by side.
 #include "kernels.hpp"
 #include "wave_ops.hpp"
 
@@ -203,8 +204,7 @@ constexpr int rec4(int cmax) { return (4 + cmax / 4) | 1; }
 // Returns the staged Gaussian's record (sensor * N + Gaussian id), -1 for lanes past the batch.
 template <int CMAX>
 __device__ __forceinline__ int64_t stage_batch(const RasterArgs& a, const RayCtx& c, int64_t b0, int64_t b1,
-                                               float4* rec) {
-  const int tid = threadIdx.x;
+                                               float4* rec, int tid) {
   const int64_t idx = b0 + tid;
   int64_t r = -1;
   if (idx < b1) {
@@ -297,7 +297,7 @@ __device__ __forceinline__ void fwd_item(const RasterArgs& a, const FwdOut& o, i
   for (int64_t b0 = c.start; b0 < c.end; b0 += kFwdBatch) {
     if (__syncthreads_count(on > 0.f) == 0) break;
     const int64_t b1 = (b0 + kFwdBatch < c.end) ? b0 + kFwdBatch : c.end;
-    if (kFwdBatch == kBlock || threadIdx.x < kFwdBatch) stage_batch<CMAX>(a, c, b0, b1, sm.rec);
+    if (kFwdBatch == kBlock || threadIdx.x < kFwdBatch) stage_batch<CMAX>(a, c, b0, b1, sm.rec, threadIdx.x);
     __syncthreads();
     const int nb = (int)(b1 - b0);
     // Branch-free over the lanes: a lane's decisions (box, alpha threshold, stop) become selects,
@@ -453,11 +453,17 @@ constexpr int kRpl = kBlock / kBwdLanes;   // rays per lane
 constexpr int kBwdBatch = 64;              // Gaussians staged per batch (one per lane of wavefront 0)
 
 template <int CMAX>
-struct BwdSmem {
-  static constexpr int kCmax = CMAX;   // the launch's channel bucket: sets the gradient row stride
+struct BwdSeg {
   float4 rec[kBwdBatch * rec4(CMAX)];
   float acc[BwdShape<CMAX>::V][kBwdBatch];
   int used[kBwdBatch];
+};
+
+template <int CMAX, int SEG = 1>
+struct BwdSmem {
+  static constexpr int kCmax = CMAX;   // the launch's channel bucket: sets the gradient row stride
+  BwdSeg<CMAX> seg[SEG];
+  float state[SEG][3][SEG > 1 ? kBlock : 1];   // per segment and ray: product of 1 - alpha, blends
   int maxlast;
   float toff;   // the item's time-offset gradient, summed over its wavefronts
 };
@@ -477,17 +483,28 @@ __device__ __forceinline__ constexpr float value_scale(int k) {
        : 1.f;
 }
 
-template <int CMAX, bool LIDAR, bool TILE, typename SM>
-__device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, int64_t tile, int pos, SM& sm) {
+// P rays per lane; SEG segments of the list walked side by side (1: the whole list).
+//
+// SEG > 1 is for launches with too few items to fill the chip, whose time is one item's serial walk:
+// the workgroup has SEG groups of 256 / P lanes, each covering all of the item's rays over one
+// segment of the list.  A first, cheaper pass takes from each segment, per ray, the product of its
+// transmittances and its blend of the feature and depth terms (the same recurrences as the walk's,
+// started from nothing); a ray's state at the far end of a segment then follows from the segments
+// behind it, and the walks proper run in parallel.
+template <int CMAX, bool LIDAR, bool TILE, int P, int SEG, typename SM>
+__device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, int64_t tile, int pos, SM& smw) {
   using SH = BwdShape<CMAX>;
   constexpr int R4 = rec4(CMAX);
-  constexpr int P = kRpl;
+  constexpr int kLanes = kBlock / P;   // of one group
+  const int seg = SEG == 1 ? 0 : (int)(threadIdx.x / kLanes);
+  auto& sm = smw.seg[seg];
   static_assert(SH::V <= 64, "channels");
   static_assert(sizeof(sm.acc) / sizeof(sm.acc[0]) >= SH::V, "accumulator rows");
   static_assert(sizeof(sm.rec) / sizeof(sm.rec[0]) >= kBwdBatch * R4, "record staging");
+  static_assert(SEG == 1 || sizeof(smw.state) / sizeof(smw.state[0]) >= SEG, "segment states");
   auto& s_acc = sm.acc;
   int* s_used = sm.used;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x - seg * kLanes, lane = tid & 63, wave = tid >> 6;   // in the group
   RayCtx c[P];
 #pragma unroll
   for (int p = 0; p < P; ++p) setup_ray<LIDAR>(a, tile, pos, c[p], (P * wave + p) * 64 + lane);
@@ -516,17 +533,19 @@ __device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, in
     }
     dATf[p] = dA * T[p];
   }
-  if (tid == 0) {
-    sm.maxlast = 0;
-    sm.toff = 0.f;
+  if (threadIdx.x == 0) {
+    smw.maxlast = 0;
+    smw.toff = 0.f;
   }
-  for (int k = tid; k < SH::V * kBwdBatch; k += kBwdLanes) (&s_acc[0][0])[k] = 0.f;
+  for (int k = tid; k < SH::V * kBwdBatch; k += kLanes) (&s_acc[0][0])[k] = 0.f;
   if (tid < kBwdBatch) s_used[tid] = 0;
   __syncthreads();
-  const int my_last = last_l[0] > last_l[1] ? last_l[0] : last_l[1];
-  if (my_last > 0) atomicMax(&sm.maxlast, my_last);
+  int my_last = last_l[0];
+#pragma unroll
+  for (int p = 1; p < P; ++p) my_last = last_l[p] > my_last ? last_l[p] : my_last;
+  if (my_last > 0 && seg == 0) atomicMax(&smw.maxlast, my_last);
   __syncthreads();
-  const int64_t n_proc = sm.maxlast;
+  const int64_t n_proc = smw.maxlast;
   __syncthreads();           // everyone has read maxlast before it can be reset by the next item
   if (n_proc == 0) {         // uniform
     stamp_done(b.sensor_done, c[0].s);
@@ -548,13 +567,104 @@ __device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, in
   const int my_slot = scatter_slot<VR>(lane, my_store);
   const int my_idx = (!LIDAR && my_slot >= kNV - 1) ? my_slot + 1 : my_slot;   // accumulator row
   float tacc = 0.f;    // camera: dL/dt of this lane's pairs (mean at time t moves with the velocity)
-  for (int64_t b0 = start + ((n_proc - 1) / kBwdBatch) * kBwdBatch; b0 >= start; b0 -= kBwdBatch) {
+  // the group's batches [lo, lo + per) (those past the list's last one are empty), back to front
+  const int n_bat = (int)((n_proc + kBwdBatch - 1) / kBwdBatch);
+  const int per = (n_bat + SEG - 1) / SEG;
+  const int lo = seg * per;
+  if constexpr (SEG > 1) {
+    float Pr[P];   // S_dot and bufD serve the pass first, then hold the walk's start
+#pragma unroll
+    for (int p = 0; p < P; ++p) Pr[p] = 1.f;
+    if (n_bat > 1) {   // uniform: with one batch there is nothing behind segment 0
+      for (int bi = lo + per - 1; bi >= lo; --bi) {
+        const int64_t b0 = start + (int64_t)bi * kBwdBatch;
+        const int64_t b1 = (b0 + kBwdBatch < start + n_proc) ? b0 + kBwdBatch : start + n_proc;
+        // the frontmost segment's state is not needed: its group only keeps the barriers
+        if (seg > 0 && tid < kBwdBatch) stage_batch<CMAX>(a, c[0], b0, b1, sm.rec, tid);
+        __syncthreads();
+        const int nb = seg > 0 ? (int)(b1 - b0) : 0;
+        for (int j = nb - 1; j >= 0; --j) {
+          const float4* r = sm.rec + j * R4;
+          const int posj = (int)(b0 + j - start);
+          bool act[P];
+          uint64_t cand[P], any = 0;
+          const float4 bx = r[2];
+#pragma unroll
+          for (int p = 0; p < P; ++p) {
+            act[p] = posj < last_l[p];
+            cand[p] = lane_mask(act[p]);
+            if (!TILE) {
+              const float bxa[4] = {bx.x, bx.y, bx.z, bx.w};
+              act[p] = act[p] && box_contains(LIDAR, c[p].px, c[p].py, bxa);
+              cand[p] = LIDAR ? lane_mask(act[p]) : cand[p] & camera_box_mask(c[p].px, c[p].py, bx);
+            }
+            any |= cand[p];
+          }
+          if (any == 0) continue;
+          const float4 m = r[0], ce = r[1], d = r[3];
+          float alpha[P];
+          uint64_t blend = 0;
+#pragma unroll
+          for (int p = 0; p < P; ++p) {
+            PairEval e;
+            eval_pair(LIDAR, c[p].px, c[p].py, c[p].t, m, ce, e);
+            alpha[p] = clamp_alpha(e.oG);
+            const bool pass = alpha[p] >= kAlphaMin;
+            blend |= cand[p] & lane_mask(pass);
+            act[p] = act[p] && pass;
+          }
+          if (blend == 0) continue;
+#pragma unroll
+          for (int p = 0; p < P; ++p) {
+            const float a_eff = act[p] ? alpha[p] : 0.f;
+            float fd = 0.f;
+#pragma unroll
+            for (int c4 = 0; c4 < CMAX / 4; ++c4) {
+              const float4 f = r[4 + c4];
+              fd = SPLAT_FMA(f.x, dF[p][4 * c4 + 0], fd);
+              fd = SPLAT_FMA(f.y, dF[p][4 * c4 + 1], fd);
+              fd = SPLAT_FMA(f.z, dF[p][4 * c4 + 2], fd);
+              fd = SPLAT_FMA(f.w, dF[p][4 * c4 + 3], fd);
+            }
+            const float gv = LIDAR ? SPLAT_FMA(d.y, c[p].t, d.x) : d.x;
+            S_dot[p] = SPLAT_FMA(a_eff, fd - S_dot[p], S_dot[p]);
+            bufD[p] = SPLAT_FMA(a_eff, gv - bufD[p], bufD[p]);
+            Pr[p] = SPLAT_FMA(-a_eff, Pr[p], Pr[p]);
+          }
+        }
+        __syncthreads();
+      }
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const int slot = (P * wave + p) * 64 + lane;
+        smw.state[seg][0][slot] = Pr[p];
+        smw.state[seg][1][slot] = S_dot[p];
+        smw.state[seg][2][slot] = bufD[p];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const int slot = (P * wave + p) * 64 + lane;
+        float Pt = 1.f;
+        S_dot[p] = bufD[p] = 0.f;
+        for (int h = SEG - 1; h > seg; --h) {   // the segments behind this one, deepest first
+          const float Ph = smw.state[h][0][slot];
+          S_dot[p] = SPLAT_FMA(Ph, S_dot[p], smw.state[h][1][slot]);
+          bufD[p] = SPLAT_FMA(Ph, bufD[p], smw.state[h][2][slot]);
+          Pt *= Ph;
+        }
+        T[p] = T[p] / Pt;
+      }
+    }
+  }
+  for (int bi = lo + per - 1; bi >= lo; --bi) {
+    const int64_t b0 = start + (int64_t)bi * kBwdBatch;
     const int64_t b1 = (b0 + kBwdBatch < start + n_proc) ? b0 + kBwdBatch : start + n_proc;
     // lane j of wavefront 0 stages Gaussian j of the batch and, after the walk, stores its
     // results: its record and gradient row are looked up now, beside the staging loads
     int64_t my_rec = -1, my_row = 0;
     if (tid < kBwdBatch) {
-      my_rec = stage_batch<CMAX>(a, c[0], b0, b1, sm.rec);
+      my_rec = stage_batch<CMAX>(a, c[0], b0, b1, sm.rec, tid);
       if (my_rec >= 0 && !split) my_row = a.entry_base[my_rec] + rect_entry(S, a.rect[my_rec], tile_local);
     }
     __syncthreads();
@@ -575,7 +685,10 @@ __device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, in
           cand[p] = LIDAR ? lane_mask(act[p]) : cand[p] & camera_box_mask(c[p].px, c[p].py, bx);
         }
       }
-      if ((cand[0] | cand[1]) == 0) continue;
+      uint64_t any = cand[0];
+#pragma unroll
+      for (int p = 1; p < P; ++p) any |= cand[p];
+      if (any == 0) continue;
       const float4 m = r[0], ce = r[1], d = r[3];
       PairEval e[P];
       float alpha[P];
@@ -686,9 +799,9 @@ __device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, in
     tacc *= -kLn2;            // the velocity terms of values 0 and 1 (see value_scale)
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) tacc += __shfl_xor(tacc, d, 64);
-    if (lane == 0) atomicAdd(&sm.toff, tacc);
+    if (lane == 0) atomicAdd(&smw.toff, tacc);
     __syncthreads();
-    if (tid == 0) atomicAdd(b.d_toff + c[0].s, sm.toff);
+    if (threadIdx.x == 0) atomicAdd(b.d_toff + c[0].s, smw.toff);
   }
   stamp_done(b.sensor_done, c[0].s);
 }
@@ -697,12 +810,31 @@ template <int CMAX, bool LIDAR, bool TILE>
 __global__ __launch_bounds__(kBwdLanes) void k_raster_bwd(RasterArgs a, BwdIn b) {
   __shared__ BwdSmem<CMAX> sm;
   if (!LIDAR) {
-    bwd_item<CMAX, false, TILE>(a, b, blockIdx.x, 0, sm);
+    bwd_item<CMAX, false, TILE, kRpl, 1>(a, b, blockIdx.x, 0, sm);
   } else {
     if ((int64_t)blockIdx.x >= (int64_t)a.n_work[0]) return;
     const int2 w = a.work[blockIdx.x];
-    bwd_item<CMAX, true, TILE>(a, b, w.x, w.y, sm);
+    bwd_item<CMAX, true, TILE, kRpl, 1>(a, b, w.x, w.y, sm);
   }
+}
+
+// Item kinds of a launch (a kernel is compiled for each).
+enum : int { kItemsCamera = 1, kItemsLidar = 2, kItemsBoth = 3, kItemsGrouped = 4 };
+
+// Segmented form: one workgroup per item of any call (camera call: tile = block; else work[block]), its
+// list in SEG segments.
+template <int CMC, int CML, int KINDS, int P, int SEG>
+__global__ __launch_bounds__(kBlock / P * SEG) void k_raster_bwd_seg(RasterArgs a, BwdIn b) {
+  __shared__ BwdSmem<cmax_max(CMC, CML), SEG> sm;
+  int2 w = make_int2((int)blockIdx.x, 0);
+  if (a.n_work) {   // uniform: not a camera call
+    if ((int64_t)blockIdx.x >= (int64_t)a.n_work[0]) return;
+    w = a.work[blockIdx.x];
+  }
+  if (KINDS == kItemsLidar || (KINDS == kItemsBoth && item_is_lidar(a, w.x)))
+    bwd_item<CML, true, false, P, SEG>(a, b, w.x, w.y, sm);
+  else
+    bwd_item<CMC, false, false, P, SEG>(a, b, w.x, 0, sm);
 }
 
 // Item kinds an adjoint queue kernel renders (the queue holds its lidar items first and its
@@ -711,8 +843,6 @@ __global__ __launch_bounds__(kBwdLanes) void k_raster_bwd(RasterArgs a, BwdIn b)
 // 76 bytes per lane in its per-item set-up instead, which measures faster than 3 waves.
 // kItemsGrouped: both kinds, the queue grouped by kind (the adjoint keeps rows): one loop over
 // the lidar part, then one over the camera part, which halves the combined kernel's spills.
-enum : int { kItemsCamera = 1, kItemsLidar = 2, kItemsBoth = 3, kItemsGrouped = 4 };
-
 template <int CMC, int CML, bool TILE, int KINDS>
 __global__ __launch_bounds__(kBwdLanes) __attribute__((amdgpu_waves_per_eu(4)))
 void k_raster_bwd_queue(RasterArgs a, BwdIn b, int32_t* counter, int n_cam) {
@@ -726,11 +856,11 @@ void k_raster_bwd_queue(RasterArgs a, BwdIn b, int32_t* counter, int n_cam) {
     for (; it < n_items; it = next_item(counter, &s_slot)) {   // the lidar items come first
       const int2 w = a.work[it];
       if (!item_is_lidar(a, w.x)) break;   // uniform over the workgroup
-      bwd_item<CML, true, TILE>(a, b, w.x, w.y, sm);
+      bwd_item<CML, true, TILE, kRpl, 1>(a, b, w.x, w.y, sm);
     }
     for (; it < n_items; it = next_item(counter, &s_slot)) {
       const int2 w = a.work[it];
-      bwd_item<CMC, false, TILE>(a, b, w.x, 0, sm);
+      bwd_item<CMC, false, TILE, kRpl, 1>(a, b, w.x, 0, sm);
     }
   } else {
     for (;;) {
@@ -738,9 +868,9 @@ void k_raster_bwd_queue(RasterArgs a, BwdIn b, int32_t* counter, int n_cam) {
       if (it >= hi) break;
       const int2 w = a.work[it];
       if (KINDS == kItemsLidar || (KINDS == kItemsBoth && item_is_lidar(a, w.x)))
-        bwd_item<CML, true, TILE>(a, b, w.x, w.y, sm);
+        bwd_item<CML, true, TILE, kRpl, 1>(a, b, w.x, w.y, sm);
       else
-        bwd_item<CMC, false, TILE>(a, b, w.x, 0, sm);
+        bwd_item<CMC, false, TILE, kRpl, 1>(a, b, w.x, 0, sm);
     }
   }
 }
@@ -840,6 +970,61 @@ static void queue_buckets(const CallView& v, int& cmc, int& cml) {
   if (c_lid > 0 && cmax_bucket(c_lid) == 8 && cmc > 8) cml = 8;
 }
 
+// Work items of a call, about (the device knows how many 256-ray chunks the lidar tiles make).
+static int64_t item_estimate(const CallView& v) {
+  const int64_t lidar_tiles = v.n_tiles - v.lidar_tile0, lidar_chunks = div_up(v.n_rays - v.lidar_ray0, SPLAT_RAYS_PER_ITEM);
+  return v.lidar_tile0 + (lidar_tiles > lidar_chunks ? lidar_tiles : lidar_chunks);
+}
+
+// The segmented adjoint takes calls whose items do not fill the chip: up to one item per compute unit
+// with 8 segments x 128 lanes, up to two with 2 x 256.  Kernel times, segmented against one walk per
+// item: camera 157 x 93 (60 tiles) 163 against 338 us, 320 x 180 (240) 112 / 227, lidar 32 x 1024
+// (128) 100 / 193, camera 480 x 270 (510) 117 / 145, lidar 128 x 1024 (512) 132 / 197; at 920 camera
+// tiles the extra pass costs more than it gives (256 / 227).  BOX calls of at most 16 channels only:
+// wider rows spill (213 registers at 32 channels, against 128 for 1024 lanes).
+constexpr int kSegChannels = 16;
+
+static int64_t segmented_items_per_cu(const CallView& v, int support) {   // 0: not segmented
+  if (support != SPLAT_SUPPORT_BOX || v.c_max > kSegChannels) return 0;
+  const int64_t per_cu = div_up(item_estimate(v), v.n_cu > 0 ? v.n_cu : 256);
+  return per_cu <= 2 ? (per_cu < 1 ? 1 : per_cu) : 0;
+}
+
+template <int CMC, int CML, int KINDS>
+static void seg_launch(int64_t items, int64_t per_cu, hipStream_t s, const RasterArgs& a, const BwdIn& b) {
+  const dim3 grid((unsigned)items);
+  if (per_cu == 1)
+    hipLaunchKernelGGL((k_raster_bwd_seg<CMC, CML, KINDS, 2, 8>), grid, dim3(kBlock / 2 * 8), 0, s, a, b);
+  else
+    hipLaunchKernelGGL((k_raster_bwd_seg<CMC, CML, KINDS, 1, 2>), grid, dim3(kBlock * 2), 0, s, a, b);
+}
+
+static hipError_t launch_bwd_seg(const CallView& v, int64_t per_cu, hipStream_t s, RasterArgs a, const BwdIn& b,
+                                 const KernelTimer& timer) {
+  const bool listed = v.queue || v.lidar;   // the items are in the work list (a camera call: the tiles in order)
+  const int64_t items = listed ? work_capacity(v.n_tiles, v.n_rays) : v.n_tiles;
+  if (items <= 0) return hipSuccess;
+  if (!listed) a.n_work = nullptr;
+  int cmc, cml;
+  queue_buckets(v, cmc, cml);
+  const int kinds = !v.has_lidar ? kItemsCamera : v.lidar_tile0 == 0 ? kItemsLidar : kItemsBoth;
+  if (timer.start) (void)hipEventRecord(timer.start, s);
+#define SEG_CASE(CM)                                                                       \
+  if (cmc == CM && cml == CM) {                                                            \
+    if (kinds == kItemsCamera) seg_launch<CM, CM, kItemsCamera>(items, per_cu, s, a, b);   \
+    else if (kinds == kItemsLidar) seg_launch<CM, CM, kItemsLidar>(items, per_cu, s, a, b); \
+    else seg_launch<CM, CM, kItemsBoth>(items, per_cu, s, a, b);                           \
+  }
+  SEG_CASE(4)
+  SEG_CASE(8)
+  SEG_CASE(16)
+#undef SEG_CASE
+  // lidars of 8 channels beside wider cameras, or a lidar of a call of wider ones: both kinds
+  if (cmc == 16 && cml == 8) seg_launch<16, 8, kItemsBoth>(items, per_cu, s, a, b);
+  if (timer.stop) (void)hipEventRecord(timer.stop, s);
+  return hipGetLastError();
+}
+
 hipError_t launch_raster_fwd(const CallView& v, const SplatGaussians& g, const SplatProjected& p,
                              const SplatTileLists& L, int support, const SplatRenderOut& out, SplatStatus* st,
                              hipStream_t s, const KernelTimer& timer) {
@@ -905,6 +1090,7 @@ hipError_t launch_raster_bwd(const CallView& v, const SplatGaussians& g, const S
           d_toff, saved.d_los};
   const int cm = cmax_bucket(v.c_max);
   if (w.stride != slot_stride(cm)) return hipErrorInvalidValue;
+  if (const int64_t per_cu = segmented_items_per_cu(v, support)) return launch_bwd_seg(v, per_cu, s, a, b, timer);
   if (v.queue) {
     const int64_t items = L.work_cap;
     if (items <= 0) return hipSuccess;
