@@ -155,8 +155,5 @@ struct FillSegments {
   }
 };
 hipError_t launch_fill_segments(const FillSegments& f, hipStream_t s);
-// exclusive scan of in[0..n) into out (may alias in); part: div_up(n, kScanTile) + 1 entries,
-// the last of which receives the total
-hipError_t launch_exclusive_scan_i64(const int64_t* in, int64_t n, int64_t* out, int64_t* part, hipStream_t s);
 
 }  // namespace splat

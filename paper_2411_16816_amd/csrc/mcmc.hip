@@ -12,6 +12,7 @@
 #include <cmath>
 
 #include "kernels.hpp"
+#include "scan.hpp"
 #include "wave_ops.hpp"
 
 namespace splat {
@@ -111,140 +112,192 @@ int splat_mcmc_regularizer(const SplatGaussians* g, float lambda_o, float lambda
 // profile integrates to the original's).  The draw is exact integer arithmetic: weights
 // floor(o * 2^24) (alive only), their exclusive scan, r = floor(u * total / 2^32) from the
 // caller's 32-bit random u, the target the first Gaussian whose inclusive sum exceeds r.
-// Passes: weights, their scan, a lookup table of the draw (for every 2^s-wide range of r the first
-// Gaussian that can be its target, one entry per four Gaussians), the draw (a short binary search
-// between two table entries, one atomic count per dead Gaussian), new opacity and scales of each
-// target (FP64), copies.
+// Passes: one scan of the opacities (weights, and the list of the dead), then three over the list of
+// the dead alone, with dense wavefronts: the draw, the new opacity and scales of each target (FP64),
+// the copies.  2M Gaussians of 30 words, a tenth dead: 104 us (18 + 28 + 16 + 41) against 185 for passes
+// over all Gaussians with a tenth of the lanes at work.
 // ---------------------------------------------------------------------------------------------
 namespace splat {
 
 constexpr float kWeightOne = 16777216.f;   // 2^24
+constexpr int kSampleLog = 12;             // the draw's first step searches up to 2^12 samples in LDS
 
-__global__ void k_reloc_weights(const float* __restrict__ o, int64_t n, float thr, int64_t* __restrict__ w,
-                                int32_t* __restrict__ counts) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float oi = o[i];
-  w[i] = oi > thr ? (int64_t)fminf(floorf(oi * kWeightOne), kWeightOne) : 0;
-  counts[i] = 0;
-}
+// The scan stores the sum before every 8th Gaussian: between two of them the draw adds the weights up
+// again, from the one or two cache lines that hold their opacities.
+constexpr int kFineLog = 3;
+inline int64_t reloc_fine(int64_t n) { return ((n - 1) >> kFineLog) + 1; }
 
-// the first j in [lo, hi] whose inclusive sum (excl[j + 1], or the total) exceeds r; the caller
-// guarantees that it lies in that range
-__device__ inline int64_t first_exceeding(const int64_t* __restrict__ excl, int64_t n, int64_t total, int64_t r,
-                                          int64_t lo, int64_t hi) {
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    const int64_t inc = mid + 1 < n ? excl[mid + 1] : total;
-    if (inc > r) hi = mid;
-    else lo = mid + 1;
-  }
-  return lo;
-}
-
-// bucket width 2^s of the lookup table: the smallest s with (total - 1) >> s < n_lut
-__device__ inline int lut_shift(int64_t total, int64_t n_lut) {
+// samples of the stored sums: every 2^s-th, the smallest s that leaves at most 2^kSampleLog
+inline int reloc_sample_shift(int64_t n_fine) {
   int s = 0;
-  while (((total - 1) >> s) >= n_lut) ++s;
+  while (((n_fine - 1) >> s) >= ((int64_t)1 << kSampleLog)) ++s;
   return s;
 }
 
-inline int64_t reloc_lut_entries(int64_t n) { return n > 4 ? (n + 3) / 4 : 1; }
-
-// lut[b] = the target of r = b << s, for b <= (total - 1) >> s
-__global__ void k_reloc_lut(const int64_t* __restrict__ excl, int64_t n, const int64_t* __restrict__ total_p,
-                            int64_t n_lut, int32_t* __restrict__ lut) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = *total_p;
-  if (total <= 0) return;
-  const int s = lut_shift(total, n_lut);
-  if (b > ((total - 1) >> s)) return;
-  lut[b] = (int32_t)first_exceeding(excl, n, total, b << s, 0, n - 1);
+// weight of a Gaussian's opacity (none for the dead)
+__device__ __forceinline__ int64_t reloc_weight(float o, float thr) {
+  return o > thr ? (int64_t)fminf(floorf(o * kWeightOne), kWeightOne) : 0;
 }
 
-// grid-stride over the Gaussians; targets are nondecreasing in r, so the target of r lies between
-// the table entries of its bucket and of the next one (the last Gaussian for the last bucket)
-__global__ __launch_bounds__(256) void k_reloc_draw(const float* __restrict__ o, int64_t n, float thr,
-                                                    const uint32_t* __restrict__ u, const int64_t* __restrict__ excl,
-                                                    const int64_t* __restrict__ total_p, int64_t n_lut,
-                                                    const int32_t* __restrict__ lut, int32_t* __restrict__ counts,
-                                                    int32_t* __restrict__ target,
-                                                    unsigned long long* __restrict__ n_moved) {
-  __shared__ unsigned int s_moved;
-  if (threadIdx.x == 0) s_moved = 0;
-  __syncthreads();
-  const int64_t total = *total_p;
-  const int s = total > 0 ? lut_shift(total, n_lut) : 0;
-  const int64_t last_b = total > 0 ? (total - 1) >> s : 0;
-  unsigned int moved = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    int32_t t = -1;
-    if (!(o[i] > thr) && total > 0) {
-      const uint64_t T = (uint64_t)total, ui = u[i];
-      const int64_t r = (int64_t)((T >> 32) * ui + (((T & 0xffffffffull) * ui) >> 32));   // < total
-      const int64_t b = r >> s;
-      const int64_t lo = lut[b], hi = b < last_b ? (int64_t)lut[b + 1] : n - 1;
-      t = (int32_t)first_exceeding(excl, n, total, r, lo, hi);
-      atomicAdd(&counts[t], 1);
-      ++moved;
+// (weight, dead) of Gaussian i
+struct LoadReloc {
+  const float* o;
+  float thr;
+  __device__ P64 operator()(int64_t i) const {
+    const float oi = o[i];
+    return P64(reloc_weight(oi, thr), (int64_t)(oi > thr ? 0 : 1));
+  }
+};
+
+// Stores the sums before every 8th Gaussian and their samples, lists the dead, and clears what the draw counts in;
+// adds the number of Gaussians that will move (the dead, unless there is no weight to draw from).
+struct RelocVisit {
+  int64_t* fine;
+  int64_t* sample;
+  int shift;
+  int32_t* dead;
+  int32_t* target;
+  int32_t* counts;
+  unsigned long long* n_moved;
+  struct In {};
+  __device__ In load(int64_t, P64) const { return In{}; }
+  __device__ void operator()(int64_t i, P64 p, P64 v, In) const {
+    if ((i & ((1 << kFineLog) - 1)) == 0) {
+      const int64_t f = i >> kFineLog;
+      fine[f] = p.a;
+      if ((f & (((int64_t)1 << shift) - 1)) == 0) sample[f >> shift] = p.a;
     }
-    target[i] = t;
+    if (v.b) dead[p.b] = (int32_t)i;
+    target[i] = -1;
+    counts[i] = 0;
   }
-  if (!n_moved) return;   // uniform
-  if (moved) atomicAdd(&s_moved, moved);
+  __device__ void finish(P64 total) const {
+    if (n_moved && total.a > 0 && total.b > 0) atomicAdd(n_moved, (unsigned long long)total.b);
+  }
+};
+
+constexpr uint32_t kFirstDraw = 0x80000000u;   // in a drawn target: the first draw of that target
+
+// Grid-stride over the dead.  r's target is the first Gaussian whose inclusive sum exceeds r: a binary
+// search over the samples, which a workgroup keeps in LDS, then 8-way steps, whose seven loads are in
+// flight together, over the 2^shift stored sums between two of them (two steps at 2M Gaussians), then the
+// eight weights after the last sum that does not exceed r.  Bound by the cache lines that a draw
+// touches (about 7); with a stored sum for every Gaussian it was 17, and 36 us instead of 28 for
+// 200k draws among 2M.
+__global__ __launch_bounds__(256) void k_reloc_draw(const float* __restrict__ o, int64_t n, float thr,
+                                                    const uint32_t* __restrict__ u, const int64_t* __restrict__ fine,
+                                                    const int64_t* __restrict__ sample, int shift,
+                                                    const P64* __restrict__ total, const int32_t* __restrict__ dead,
+                                                    int32_t* __restrict__ counts, int32_t* __restrict__ target,
+                                                    uint32_t* __restrict__ drawn) {
+  __shared__ int64_t s_sample[1 << kSampleLog];
+  const P64 tot = *total;
+  if (tot.a <= 0 || (int64_t)blockIdx.x * blockDim.x >= tot.b) return;   // uniform
+  const int64_t n_fine = ((n - 1) >> kFineLog) + 1;
+  const int n_sample = (int)((n_fine - 1) >> shift) + 1;
+  for (int k = threadIdx.x; k < n_sample; k += blockDim.x) s_sample[k] = sample[k];
   __syncthreads();
-  if (threadIdx.x == 0 && s_moved) atomicAdd(n_moved, (unsigned long long)s_moved);
-}
-
-__global__ void k_reloc_update(const float* __restrict__ o, const float* __restrict__ ls, int64_t n,
-                               const int32_t* __restrict__ counts, int n_max, float* __restrict__ new_o,
-                               float* __restrict__ new_ls) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n || counts[i] == 0) return;
-  int N = counts[i] + 1;
-  N = N < n_max ? N : n_max;
-  const double od = o[i];
-  const double on = 1.0 - pow(1.0 - od, 1.0 / N);
-  double denom = 0.0, c = 1.0, p = 1.0;   // c = C(N, k), p = o'^k
-  for (int k = 1; k <= N; ++k) {
-    c = c * (double)(N - k + 1) / (double)k;
-    p *= on;
-    denom += ((k & 1) ? c : -c) * p / sqrt((double)k);
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < tot.b; j += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = dead[j];
+    const uint64_t T = (uint64_t)tot.a, ui = u[i];
+    const int64_t r = (int64_t)((T >> 32) * ui + (((T & 0xffffffffull) * ui) >> 32));   // < total
+    int lo = 0, hi = n_sample;   // sample[lo] <= r < sample[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (s_sample[mid] <= r) lo = mid;
+      else hi = mid;
+    }
+    int64_t f = (int64_t)lo << shift, sum = s_sample[lo];
+    for (int s = shift; s > 0;) {
+      const int d = s < 3 ? s : 3;
+      s -= d;
+      int64_t e[7];
+#pragma unroll
+      for (int m = 0; m < 7; ++m) {
+        const int64_t q = f + ((int64_t)(m + 1) << s);
+        e[m] = fine[q < n_fine ? q : n_fine - 1];
+      }
+      int below = 0;   // the sums do not decrease
+#pragma unroll
+      for (int m = 0; m < 7; ++m)
+        if (m + 1 < (1 << d) && f + ((int64_t)(m + 1) << s) < n_fine && e[m] <= r) {
+          below = m + 1;
+          sum = e[m];
+        }
+      f += (int64_t)below << s;
+    }
+    const int64_t t0 = f << kFineLog;
+    float w[1 << kFineLog];
+#pragma unroll
+    for (int m = 0; m < (1 << kFineLog); ++m) w[m] = o[t0 + m < n ? t0 + m : n - 1];
+    int t = 0;   // weights that leave the sum at r or below
+#pragma unroll
+    for (int m = 0; m < (1 << kFineLog) - 1; ++m) {
+      sum += reloc_weight(w[m], thr);
+      t += sum <= r && t0 + m + 1 < n;
+    }
+    const int64_t tg = t0 + t;
+    target[i] = (int32_t)tg;
+    drawn[j] = (uint32_t)tg | (atomicAdd(&counts[tg], 1) == 0 ? kFirstDraw : 0u);
   }
-  const double lf = log(od / denom);
-  new_o[i] = (float)on;
-  for (int d = 0; d < 3; ++d) new_ls[3 * i + d] = (float)((double)ls[3 * i + d] + lf);
 }
 
-__global__ void k_reloc_apply(SplatGaussianState g, const int32_t* __restrict__ target,
-                              const int32_t* __restrict__ counts, const float* __restrict__ new_o,
-                              const float* __restrict__ new_ls) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.n) return;
-  const int64_t t = target[i];
-  if (t >= 0) {   // a dead Gaussian becomes a copy of its (alive, never written here) target
-    for (int d = 0; d < 3; ++d) g.means[3 * i + d] = g.means[3 * t + d];
-    for (int d = 0; d < 4; ++d) g.quats[4 * i + d] = g.quats[4 * t + d];
-    if (g.velocities)
-      for (int d = 0; d < 3; ++d) g.velocities[3 * i + d] = g.velocities[3 * t + d];
+// The first to have drawn a target (one of the dead per target) writes its new opacity and scales
+__global__ __launch_bounds__(256) void k_reloc_update(float* __restrict__ o, float* __restrict__ ls,
+                                                      const P64* __restrict__ total, const uint32_t* __restrict__ drawn,
+                                                      const int32_t* __restrict__ counts, int n_max) {
+  const P64 tot = *total;
+  if (tot.a <= 0) return;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < tot.b; j += (int64_t)gridDim.x * blockDim.x) {
+    const uint32_t t = drawn[j];
+    if (!(t & kFirstDraw)) continue;
+    const int64_t i = t & ~kFirstDraw;
+    int N = counts[i] + 1;
+    N = N < n_max ? N : n_max;
+    const double od = o[i];
+    const double on = 1.0 - pow(1.0 - od, 1.0 / N);
+    double denom = 0.0, c = 1.0, p = 1.0;   // c = C(N, k), p = o'^k
+    for (int k = 1; k <= N; ++k) {
+      c = c * (double)(N - k + 1) / (double)k;
+      p *= on;
+      denom += ((k & 1) ? c : -c) * p / sqrt((double)k);
+    }
+    const double lf = log(od / denom);
+    o[i] = (float)on;
+    for (int d = 0; d < 3; ++d) ls[3 * i + d] = (float)((double)ls[3 * i + d] + lf);
+  }
+}
+
+// Every dead Gaussian becomes a copy of its target (alive, so not written here): 16 lanes to one, of
+// which 14 take a word of its geometry each, and all of them its features in turn.  200k rows of 30
+// words among 2M: 41 us, 78 MB read (random lines) and 49 MB written; two rows in flight: 45.
+constexpr int kCopyLanes = 16;
+
+__global__ __launch_bounds__(256) void k_reloc_copy(SplatGaussianState g, const P64* __restrict__ total,
+                                                    const int32_t* __restrict__ dead, const uint32_t* __restrict__ drawn) {
+  const P64 tot = *total;
+  if (tot.a <= 0) return;
+  const int w = threadIdx.x % kCopyLanes;
+  float* const base = w < 3 ? g.means : w < 7 ? g.quats : w < 8 ? g.opacities : w < 11 ? g.log_scales : w < 14 ? g.velocities : nullptr;
+  const int64_t row = w < 3 ? 3 : w < 7 ? 4 : w < 8 ? 1 : 3;
+  const int col = w < 3 ? w : w < 7 ? w - 3 : w < 8 ? 0 : w < 11 ? w - 8 : w - 11;
+  const int64_t step = (int64_t)gridDim.x * (blockDim.x / kCopyLanes);
+  for (int64_t j = (int64_t)blockIdx.x * (blockDim.x / kCopyLanes) + threadIdx.x / kCopyLanes; j < tot.b; j += step) {
+    const int64_t i = dead[j], t = drawn[j] & ~kFirstDraw;
+    if (base) base[i * row + col] = base[t * row + col];
     if (g.features)
-      for (int d = 0; d < g.c_total; ++d) g.features[i * g.c_total + d] = g.features[t * g.c_total + d];
-    g.opacities[i] = new_o[t];
-    for (int d = 0; d < 3; ++d) g.log_scales[3 * i + d] = new_ls[3 * t + d];
-  } else if (counts[i] > 0) {
-    g.opacities[i] = new_o[i];
-    for (int d = 0; d < 3; ++d) g.log_scales[3 * i + d] = new_ls[3 * i + d];
+      for (int d = w; d < g.c_total; d += kCopyLanes) g.features[i * g.c_total + d] = g.features[t * g.c_total + d];
   }
 }
 
 struct RelocWs {
-  int64_t* w;
-  int64_t* part;
+  int64_t* fine;
+  P64* part;
   int32_t* counts;
   int32_t* target;
-  int32_t* lut;
-  float* new_o;
-  float* new_ls;
+  int32_t* dead;
+  uint32_t* drawn;
+  int64_t* sample;
   size_t bytes;
 };
 
@@ -257,13 +310,13 @@ inline RelocWs carve_reloc(void* base, int64_t n) {
     off += (bytes + 255) / 256 * 256;
     return p;
   };
-  r.w = (int64_t*)take(n * sizeof(int64_t));
-  r.part = (int64_t*)take((div_up(n, kScanTile) + 1) * sizeof(int64_t));
+  r.fine = (int64_t*)take(reloc_fine(n) * sizeof(int64_t));
+  r.part = (P64*)take((div_up(n, scan_tile<P64>()) + 1) * sizeof(P64));
   r.counts = (int32_t*)take(n * sizeof(int32_t));
   r.target = (int32_t*)take(n * sizeof(int32_t));
-  r.lut = (int32_t*)take(reloc_lut_entries(n) * sizeof(int32_t));
-  r.new_o = (float*)take(n * sizeof(float));
-  r.new_ls = (float*)take(3 * n * sizeof(float));
+  r.dead = (int32_t*)take(n * sizeof(int32_t));
+  r.drawn = (uint32_t*)take(n * sizeof(uint32_t));
+  r.sample = (int64_t*)take((((reloc_fine(n) - 1) >> reloc_sample_shift(reloc_fine(n))) + 1) * sizeof(int64_t));
   r.bytes = off;
   return r;
 }
@@ -289,23 +342,20 @@ int splat_mcmc_relocate(const SplatGaussianState* g, const uint32_t* u, float de
   hipStream_t s = (hipStream_t)stream;
   RelocWs w = carve_reloc(ws, g->n);
   int32_t* tgt = target ? target : w.target;
-  const unsigned nb = (unsigned)div_up(g->n, 256);
-  hipLaunchKernelGGL(k_reloc_weights, dim3(nb), dim3(256), 0, s, (const float*)g->opacities, g->n, dead_opacity, w.w,
-                     w.counts);
-  if (launch_exclusive_scan_i64(w.w, g->n, w.w, w.part, s) != hipSuccess) return SPLAT_ERR_DEVICE;
-  const int64_t* excl = w.w;
-  const int64_t* total = w.part + div_up(g->n, kScanTile);
-  const int64_t n_lut = reloc_lut_entries(g->n);
-  hipLaunchKernelGGL(k_reloc_lut, dim3((unsigned)div_up(n_lut, 256)), dim3(256), 0, s, excl, g->n, total, n_lut,
-                     w.lut);
-  // a bounded grid: one atomic per workgroup on the shared count
-  const unsigned nd = nb < 2048 ? nb : 2048;
-  hipLaunchKernelGGL(k_reloc_draw, dim3(nd), dim3(256), 0, s, (const float*)g->opacities, g->n, dead_opacity, u,
-                     excl, total, n_lut, (const int32_t*)w.lut, w.counts, tgt, n_relocated);
-  hipLaunchKernelGGL(k_reloc_update, dim3(nb), dim3(256), 0, s, (const float*)g->opacities,
-                     (const float*)g->log_scales, g->n, (const int32_t*)w.counts, (int)n_max, w.new_o, w.new_ls);
-  hipLaunchKernelGGL(k_reloc_apply, dim3(nb), dim3(256), 0, s, *g, (const int32_t*)tgt, (const int32_t*)w.counts,
-                     (const float*)w.new_o, (const float*)w.new_ls);
+  const int shift = reloc_sample_shift(reloc_fine(g->n));
+  if (device_scan<P64>(LoadReloc{g->opacities, dead_opacity}, g->n, (P64*)nullptr, w.part, s,
+                       RelocVisit{w.fine, w.sample, shift, w.dead, tgt, w.counts, n_relocated}) != hipSuccess)
+    return SPLAT_ERR_DEVICE;
+  const P64* total = w.part + div_up(g->n, scan_tile<P64>());
+  // grids for any number of dead: workgroups past it leave at once
+  const int64_t nb = div_up(g->n, 256), nc = div_up(g->n, 256 / kCopyLanes);
+  hipLaunchKernelGGL(k_reloc_draw, dim3((unsigned)(nb < 1024 ? nb : 1024)), dim3(256), 0, s,
+                     (const float*)g->opacities, g->n, dead_opacity, u, (const int64_t*)w.fine, (const int64_t*)w.sample,
+                     shift, total, (const int32_t*)w.dead, w.counts, tgt, w.drawn);
+  hipLaunchKernelGGL(k_reloc_update, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(256), 0, s, g->opacities,
+                     g->log_scales, total, (const uint32_t*)w.drawn, (const int32_t*)w.counts, (int)n_max);
+  hipLaunchKernelGGL(k_reloc_copy, dim3((unsigned)(nc < 8192 ? nc : 8192)), dim3(256), 0, s, *g, total,
+                     (const int32_t*)w.dead, (const uint32_t*)w.drawn);
   return hipGetLastError() == hipSuccess ? SPLAT_OK : SPLAT_ERR_DEVICE;
 }
 
