@@ -157,7 +157,8 @@ typedef struct SplatRigLayout {
 } SplatRigLayout;
 
 /* Projected records, one per (sensor, Gaussian): record = (s - first) * n + gaussian.
- * Device arrays, caller-allocated with count * n records. */
+ * Device arrays, caller-allocated with count * n records.  A culled record (n_tiles = 0) has no other
+ * defined field. */
 typedef struct SplatProjected {
   int64_t n_records;
   float* mv;        /* [n_records,4] mean (u,v) | (phi,omega), and its velocity               */
@@ -179,7 +180,7 @@ typedef struct SplatTileLists {
   int64_t k_cap;          /* capacity of gauss[], 0 <= k_cap < 2^32                           */
   int32_t* gauss;         /* [k_cap] Gaussian ids, grouped by tile, by (depth, id) inside      */
   int64_t* tile_range;    /* [n_tiles, 2] [start, end) into gauss (16-byte aligned)           */
-  int64_t* entry_base;    /* [count * N] written by bin_sort for records with n_tiles > 0:
+  int64_t* entry_base;    /* [count * N] defined by bin_sort for records with n_tiles > 0:
                              the number of the record's first (tile, Gaussian) entry.  Entries
                              are numbered record by record in record order, each record's tiles
                              in the row-major order of its rectangle, so record r owns the

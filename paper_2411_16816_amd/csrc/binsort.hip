@@ -30,6 +30,7 @@
 // depends on inter-workgroup forward progress.
 #include "kernels.hpp"
 #include "scan.hpp"
+#include "wave_ops.hpp"
 
 namespace splat {
 
@@ -418,6 +419,7 @@ struct VisibleVisit {
   int64_t* scalars;
   int64_t k_cap;
   SplatStatus* st;
+  static constexpr int kBatch = 8;
   struct In {
     int4 rc;
     unsigned long long dk;
@@ -431,8 +433,8 @@ struct VisibleVisit {
     return in;
   }
   __device__ void operator()(int64_t i, P64 p, P64 v, const In& in) const {
+    if (line_seen<int64_t>(__ballot(v.a != 0), i)) entry_base[i] = p.b;
     if (v.a == 0) return;
-    entry_base[i] = p.b;
     const DevSensor& S = sens[record_sensor(i, N, count)];
     const StSpan sp = st_span(S, in.rc);
     const uint64_t n_st = (uint64_t)(sp.nr * (sp.nc0 + sp.nc1));
@@ -475,6 +477,7 @@ struct LoadPackedCount {
 struct CoarseCount {
   int64_t* scalars;
   int64_t cap;
+  static constexpr int kBatch = 4;
   struct In {};
   template <typename T>
   __device__ In load(int64_t, T) const { return In{}; }
@@ -604,6 +607,7 @@ struct LoadCountX {
 // Closing step of the scan of item counts over supertiles: the count array's size.
 struct ItemsVisit {
   int64_t* scalars;
+  static constexpr int kBatch = 4;
   struct In {};
   template <typename T>
   __device__ In load(int64_t, T) const { return In{}; }

@@ -139,13 +139,13 @@ __device__ __forceinline__ int64_t reloc_weight(float o, float thr) {
   return o > thr ? (int64_t)fminf(floorf(o * kWeightOne), kWeightOne) : 0;
 }
 
-// (weight, dead) of Gaussian i
+// (dead, weight) of Gaussian i
 struct LoadReloc {
   const float* o;
   float thr;
   __device__ P64 operator()(int64_t i) const {
     const float oi = o[i];
-    return P64(reloc_weight(oi, thr), (int64_t)(oi > thr ? 0 : 1));
+    return P64((int64_t)(oi > thr ? 0 : 1), reloc_weight(oi, thr));
   }
 };
 
@@ -159,20 +159,21 @@ struct RelocVisit {
   int32_t* target;
   int32_t* counts;
   unsigned long long* n_moved;
+  static constexpr int kBatch = 4;
   struct In {};
   __device__ In load(int64_t, P64) const { return In{}; }
   __device__ void operator()(int64_t i, P64 p, P64 v, In) const {
     if ((i & ((1 << kFineLog) - 1)) == 0) {
       const int64_t f = i >> kFineLog;
-      fine[f] = p.a;
-      if ((f & (((int64_t)1 << shift) - 1)) == 0) sample[f >> shift] = p.a;
+      fine[f] = p.b;
+      if ((f & (((int64_t)1 << shift) - 1)) == 0) sample[f >> shift] = p.b;
     }
-    if (v.b) dead[p.b] = (int32_t)i;
+    if (v.a) dead[p.a] = (int32_t)i;
     target[i] = -1;
     counts[i] = 0;
   }
   __device__ void finish(P64 total) const {
-    if (n_moved && total.a > 0 && total.b > 0) atomicAdd(n_moved, (unsigned long long)total.b);
+    if (n_moved && total.b > 0 && total.a > 0) atomicAdd(n_moved, (unsigned long long)total.a);
   }
 };
 
@@ -192,14 +193,14 @@ __global__ __launch_bounds__(256) void k_reloc_draw(const float* __restrict__ o,
                                                     uint32_t* __restrict__ drawn) {
   __shared__ int64_t s_sample[1 << kSampleLog];
   const P64 tot = *total;
-  if (tot.a <= 0 || (int64_t)blockIdx.x * blockDim.x >= tot.b) return;   // uniform
+  if (tot.b <= 0 || (int64_t)blockIdx.x * blockDim.x >= tot.a) return;   // uniform
   const int64_t n_fine = ((n - 1) >> kFineLog) + 1;
   const int n_sample = (int)((n_fine - 1) >> shift) + 1;
   for (int k = threadIdx.x; k < n_sample; k += blockDim.x) s_sample[k] = sample[k];
   __syncthreads();
-  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < tot.b; j += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < tot.a; j += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = dead[j];
-    const uint64_t T = (uint64_t)tot.a, ui = u[i];
+    const uint64_t T = (uint64_t)tot.b, ui = u[i];
     const int64_t r = (int64_t)((T >> 32) * ui + (((T & 0xffffffffull) * ui) >> 32));   // < total
     int lo = 0, hi = n_sample;   // sample[lo] <= r < sample[hi]
     while (hi - lo > 1) {
@@ -247,8 +248,8 @@ __global__ __launch_bounds__(256) void k_reloc_update(float* __restrict__ o, flo
                                                       const P64* __restrict__ total, const uint32_t* __restrict__ drawn,
                                                       const int32_t* __restrict__ counts, int n_max) {
   const P64 tot = *total;
-  if (tot.a <= 0) return;
-  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < tot.b; j += (int64_t)gridDim.x * blockDim.x) {
+  if (tot.b <= 0) return;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < tot.a; j += (int64_t)gridDim.x * blockDim.x) {
     const uint32_t t = drawn[j];
     if (!(t & kFirstDraw)) continue;
     const int64_t i = t & ~kFirstDraw;
@@ -276,13 +277,13 @@ constexpr int kCopyLanes = 16;
 __global__ __launch_bounds__(256) void k_reloc_copy(SplatGaussianState g, const P64* __restrict__ total,
                                                     const int32_t* __restrict__ dead, const uint32_t* __restrict__ drawn) {
   const P64 tot = *total;
-  if (tot.a <= 0) return;
+  if (tot.b <= 0) return;
   const int w = threadIdx.x % kCopyLanes;
   float* const base = w < 3 ? g.means : w < 7 ? g.quats : w < 8 ? g.opacities : w < 11 ? g.log_scales : w < 14 ? g.velocities : nullptr;
   const int64_t row = w < 3 ? 3 : w < 7 ? 4 : w < 8 ? 1 : 3;
   const int col = w < 3 ? w : w < 7 ? w - 3 : w < 8 ? 0 : w < 11 ? w - 8 : w - 11;
   const int64_t step = (int64_t)gridDim.x * (blockDim.x / kCopyLanes);
-  for (int64_t j = (int64_t)blockIdx.x * (blockDim.x / kCopyLanes) + threadIdx.x / kCopyLanes; j < tot.b; j += step) {
+  for (int64_t j = (int64_t)blockIdx.x * (blockDim.x / kCopyLanes) + threadIdx.x / kCopyLanes; j < tot.a; j += step) {
     const int64_t i = dead[j], t = drawn[j] & ~kFirstDraw;
     if (base) base[i * row + col] = base[t * row + col];
     if (g.features)

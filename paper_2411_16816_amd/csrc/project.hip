@@ -5,7 +5,8 @@
 // One thread per Gaussian.  Its parameters are read once (coalesced: consecutive threads read
 // consecutive rows) and projected into every sensor of the call, so a batched call over S
 // sensors reads the Gaussian arrays once instead of S times.  Records are written SoA
-// (record = sensor * N + gaussian); culled records only write n_tiles = 0.
+// (record = sensor * N + gaussian).  A culled record has n_tiles = 0; its other fields are zeroed where they
+// share a cache line with a visible record's, and not written elsewhere.
 #include "kernels.hpp"
 #include "wave_ops.hpp"
 
@@ -64,13 +65,18 @@ __global__ __launch_bounds__(256) void k_project(const DevSensor* __restrict__ s
     const int64_t r = (int64_t)k * g.n + i;
     n_tiles[r] = o.n_tiles;
     nonfin += o.nonfinite ? 1u : 0u;
-    if (o.n_tiles > 0) {
-      mv[r] = make_float4(o.mean[0], o.mean[1], o.vel[0], o.vel[1]);
-      cn[r] = make_float4(o.conic[0], o.conic[1], o.conic[2], o.o_eff);
-      box[r] = make_float4(o.box[0], o.box[1], o.box[2], o.box[3]);
-      dv[r] = make_float2(o.depth, o.v_r);
-      dkey[r] = depth_key(sens[k], G.mu);
-      rect[r] = make_int4(o.rect[0], o.rect[1], o.rect[2], o.rect[3]);
+    const bool seen = o.n_tiles > 0;
+    const uint64_t mask = __ballot(seen);
+    if (line_seen<float4>(mask, r)) {
+      const float z = 0.f;
+      mv[r] = seen ? make_float4(o.mean[0], o.mean[1], o.vel[0], o.vel[1]) : make_float4(z, z, z, z);
+      cn[r] = seen ? make_float4(o.conic[0], o.conic[1], o.conic[2], o.o_eff) : make_float4(z, z, z, z);
+      box[r] = seen ? make_float4(o.box[0], o.box[1], o.box[2], o.box[3]) : make_float4(z, z, z, z);
+      rect[r] = seen ? make_int4(o.rect[0], o.rect[1], o.rect[2], o.rect[3]) : make_int4(0, 0, 0, 0);
+    }
+    if (line_seen<float2>(mask, r)) {
+      dv[r] = seen ? make_float2(o.depth, o.v_r) : make_float2(0.f, 0.f);
+      dkey[r] = seen ? depth_key(sens[k], G.mu) : 0ull;
     }
   }
   if (nonfin && st) atomicAdd(&st->n_nonfinite, nonfin);

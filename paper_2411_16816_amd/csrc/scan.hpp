@@ -6,14 +6,6 @@
 
 namespace splat {
 
-__device__ __forceinline__ int64_t shfl_up_i64(int64_t v, int d) {
-  int lo = __shfl_up((int)(uint32_t)(uint64_t)v, d, 64);
-  int hi = __shfl_up((int)(uint32_t)((uint64_t)v >> 32), d, 64);
-  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
-}
-__device__ __forceinline__ uint32_t shfl_up_t(uint32_t v, int d) { return (uint32_t)__shfl_up((int)v, d, 64); }
-__device__ __forceinline__ int64_t shfl_up_t(int64_t v, int d) { return shfl_up_i64(v, d); }
-
 // Two int64 counters scanned together (trivially constructible, so it can live in LDS).
 struct P64 {
   int64_t a, b;
@@ -28,30 +20,87 @@ struct P64 {
 };
 __device__ __forceinline__ P64 operator+(P64 x, const P64& y) { return x += y; }
 __device__ __forceinline__ P64 operator-(P64 x, const P64& y) { return P64(x.a - y.a, x.b - y.b); }
-__device__ __forceinline__ P64 shfl_up_t(P64 v, int d) { return P64(shfl_up_i64(v.a, d), shfl_up_i64(v.b, d)); }
 
-// exclusive scan across a 256-thread block; `tmp` holds 4 entries
+// What a wavefront scans in place of T: a pair whose first member counts elements (at most 2^15 to a
+// block) and whose second stays below 2^47 over a block is one 64-bit sum, the count from bit 48 on.
+__device__ __forceinline__ uint32_t scan_pack(uint32_t x) { return x; }
+__device__ __forceinline__ int64_t scan_pack(int64_t x) { return x; }
+__device__ __forceinline__ int64_t scan_pack(P64 x) { return (int64_t)(((uint64_t)x.a << 48) + (uint64_t)x.b); }
 template <typename T>
-__device__ T block_exclusive_scan(T v, T* tmp, T& total) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  T x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    T y = shfl_up_t(x, o);
-    if (lane >= o) x += y;
+struct ScanLocal {
+  using type = T;
+  static __device__ __forceinline__ T unpack(T x) { return x; }
+};
+template <>
+struct ScanLocal<P64> {
+  using type = int64_t;
+  static __device__ __forceinline__ P64 unpack(int64_t x) {
+    const int64_t b = (int64_t)((uint64_t)x << 16) >> 16;
+    return P64((x - b) >> 48, b);
   }
-  if (lane == 63) tmp[wid] = x;
-  __syncthreads();
+};
+
+// x of the lane that a DPP step names, zero where it names none
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int64_t dpp_from(int64_t x) {
+  const uint32_t lo = dpp_from<CTRL, ROWS>((uint32_t)(uint64_t)x);
+  const uint32_t hi = dpp_from<CTRL, ROWS>((uint32_t)((uint64_t)x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ P64 dpp_from(P64 x) {
+  return P64(dpp_from<CTRL, ROWS>(x.a), dpp_from<CTRL, ROWS>(x.b));
+}
+
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+__device__ __forceinline__ int64_t last_lane(int64_t x) {
+  return (int64_t)(((uint64_t)last_lane((uint32_t)((uint64_t)x >> 32)) << 32) | last_lane((uint32_t)(uint64_t)x));
+}
+__device__ __forceinline__ P64 last_lane(P64 x) { return P64(last_lane(x.a), last_lane(x.b)); }
+
+// Inclusive scan across the wavefront (every lane active): shifts by 1, 2, 4 and 8 inside the rows of 16
+// lanes, then the last lane of a row added to the rows after it.  All on the vector units: shuffles
+// through LDS are a chain of six LDS latencies.
+template <typename T>
+__device__ __forceinline__ T wave_inclusive_scan(T x) {
+  x += dpp_from<0x111, 0xf>(x);
+  x += dpp_from<0x112, 0xf>(x);
+  x += dpp_from<0x114, 0xf>(x);
+  x += dpp_from<0x118, 0xf>(x);
+  x += dpp_from<0x142, 0xa>(x);
+  x += dpp_from<0x143, 0xc>(x);
+  return x;
+}
+
+// the sum of the WAVES entries of `sums`, and of those before entry w
+template <int WAVES, typename T>
+__device__ __forceinline__ T sum_before(const T* sums, int w, T& total) {
   T pre = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    T s = tmp[w];
-    pre += (w < wid) ? s : (T)0;
+  for (int k = 0; k < WAVES; ++k) {
+    const T s = sums[k];
+    pre += k < w ? s : (T)0;
     tot += s;
   }
   total = tot;
+  return pre;
+}
+
+// exclusive scan across a block of WAVES wavefronts; `tmp` holds one entry per wavefront
+template <typename T, int WAVES = 4>
+__device__ T block_exclusive_scan(T v, T* tmp, T& total) {
+  const int w = threadIdx.x >> 6;
+  const T x = wave_inclusive_scan(v);
+  if ((threadIdx.x & 63) == 63) tmp[w] = x;
   __syncthreads();
-  return pre + x - v;
+  T pre = sum_before<WAVES>(tmp, w, total);
+  __syncthreads();
+  pre += x;
+  return pre - v;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -70,12 +119,21 @@ __device__ __forceinline__ int64_t scan_count(const int64_t* n_dev, int64_t n) {
   const int64_t m = *n_dev;
   return m < 0 ? 0 : (m < n ? m : n);
 }
-// Elements per thread and per block of a scan over T: 16-byte elements take half as many, so
-// that a block's LDS tile stays at 34 KB (four blocks per compute unit).
+// Elements per thread and per block of a scan over T.  Pairs take half as many: the visit of the visible
+// records, which follows the scan of its block, is then split over twice the blocks (10.5M records: 112 us
+// against 140).
 template <typename T>
 constexpr int scan_items() { return sizeof(T) > 8 ? kScanItems / 2 : kScanItems; }
 template <typename T>
 constexpr int scan_tile() { return kScanThreads * scan_items<T>(); }
+
+// Element of a lane's r-th row: wavefront w of a block owns scan_items x 64 consecutive elements of the
+// block's tile, row by row.
+template <typename T>
+__device__ __forceinline__ int64_t scan_element(int r) {
+  return (int64_t)blockIdx.x * scan_tile<T>() + (int64_t)((threadIdx.x >> 6) * scan_items<T>() + r) * 64 +
+         (threadIdx.x & 63);
+}
 
 template <typename T>
 __device__ __forceinline__ int64_t scan_last_block(int64_t n_eff) { return n_eff > 0 ? (n_eff - 1) / scan_tile<T>() : 0; }
@@ -84,23 +142,24 @@ template <typename T, typename Load>
 __global__ __launch_bounds__(256) void k_scan_reduce(Load ld, int64_t n, const int64_t* n_dev, T* __restrict__ part) {
   __shared__ T tmp[4];
   const int64_t n_eff = scan_count(n_dev, n);
-  constexpr int kItems = scan_items<T>();
-  const int64_t base = (int64_t)blockIdx.x * scan_tile<T>();   // < n: the grid has div_up(n, tile) blocks
-  if ((int64_t)blockIdx.x > scan_last_block<T>(n_eff)) {      // uniform: contributes nothing
+  if ((int64_t)blockIdx.x > scan_last_block<T>(n_eff)) {   // uniform: contributes nothing
     if (threadIdx.x == 0) part[blockIdx.x] = (T)0;
     return;
   }
   const int64_t hi = n_eff > 0 ? n_eff - 1 : 0;
   T acc = 0;
   // indices clamped into [0, n_eff): every load is issued unconditionally, back to back
-#pragma unroll 4
-  for (int r = 0; r < kItems; ++r) {
-    const int64_t i = base + (int64_t)r * kScanThreads + threadIdx.x;
+#pragma unroll
+  for (int r = 0; r < scan_items<T>(); ++r) {
+    const int64_t i = scan_element<T>(r);
     const T x = ld(i < hi ? i : hi);
     acc += i < n_eff ? x : (T)0;
   }
+  acc = wave_inclusive_scan(acc);
+  if ((threadIdx.x & 63) == 63) tmp[threadIdx.x >> 6] = acc;
+  __syncthreads();
   T total;
-  block_exclusive_scan<T>(acc, tmp, total);
+  sum_before<4>(tmp, 0, total);
   if (threadIdx.x == 0) part[blockIdx.x] = total;
 }
 
@@ -108,26 +167,49 @@ __global__ __launch_bounds__(256) void k_scan_reduce(Load ld, int64_t n, const i
 // launch fewer); beyond it a single block scans the totals first.
 constexpr int64_t kScanFusedBlocks = 4096;
 
-// single block: exclusive scan of part[0..nb) in place, part[nb] = total
+// single block: exclusive scan of part[0..nb) in place, part[nb] = total.  4096 entries at a time, each
+// wavefront four consecutive rows of 64; a chain of load latencies (8160 sums in two steps 4.7 us, in 32 steps of 256 entries 17).
+constexpr int kPartialWaves = 16, kPartialRows = 4;
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_scan_partials(T* __restrict__ part, int64_t nb) {
-  __shared__ T tmp[4];
+__global__ __launch_bounds__(64 * kPartialWaves) void k_scan_partials(T* __restrict__ part, int64_t nb) {
+  __shared__ T tmp[kPartialWaves];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   T carry = 0;
-  for (int64_t b0 = 0; b0 < nb; b0 += 256) {
-    int64_t i = b0 + threadIdx.x;
-    T v = i < nb ? part[i] : (T)0;
+  for (int64_t b0 = 0; b0 < nb; b0 += kPartialWaves * kPartialRows * 64) {
+    const int64_t i0 = b0 + w * kPartialRows * 64 + lane;
+    T v[kPartialRows], pre[kPartialRows];
+#pragma unroll
+    for (int r = 0; r < kPartialRows; ++r) {
+      const int64_t i = i0 + r * 64;
+      const T x = part[i < nb ? i : nb - 1];
+      v[r] = i < nb ? x : (T)0;
+    }
+    T run = 0;
+#pragma unroll
+    for (int r = 0; r < kPartialRows; ++r) {
+      const T x = wave_inclusive_scan(v[r]);
+      pre[r] = run + x - v[r];
+      run += last_lane(x);
+    }
+    if (lane == 0) tmp[w] = run;
+    __syncthreads();
     T total;
-    T ex = block_exclusive_scan<T>(v, tmp, total);
-    if (i < nb) part[i] = carry + ex;
+    const T before = carry + sum_before<kPartialWaves>(tmp, w, total);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kPartialRows; ++r)
+      if (i0 + r * 64 < nb) part[i0 + r * 64] = before + pre[r];
     carry += total;
   }
   if (threadIdx.x == 0) part[nb] = carry;
 }
 
 // Per-element work of a scan, in two phases so that the loads of several elements are issued
-// before any of their stores: In load(i, value) reads what element i needs, then
+// before any of their stores: In load(i, value) reads what element i needs (kBatch rows' at a time), then
 // operator()(i, prefix, value, in) writes; finish(total) runs once with the grand total.
 struct NoVisit {
+  static constexpr int kBatch = 4;
   struct In {};
   template <typename T>
   __device__ In load(int64_t, T) const { return In{}; }
@@ -140,6 +222,7 @@ struct NoVisit {
 // Writes the grand total to *dst (no per-element work).
 struct StoreTotal {
   int64_t* dst;
+  static constexpr int kBatch = 4;
   struct In {};
   template <typename T>
   __device__ In load(int64_t, T) const { return In{}; }
@@ -156,76 +239,76 @@ struct StoreTotal {
 template <typename T, typename Load, typename Visit>
 __global__ __launch_bounds__(256) void k_scan_down(Load ld, int64_t n, const int64_t* n_dev, T* __restrict__ part,
                                                    int64_t nb, bool fused, T* __restrict__ out, Visit vis) {
-  // element li of the tile lives at pad(li) = li + li / 16: a thread's 16 consecutive
-  // elements then start 17 apart, which spreads the per-thread pass over the LDS banks
-  constexpr int kItems = scan_items<T>();
-  constexpr int kTile = scan_tile<T>();
-  __shared__ T tile[kTile + kTile / kItems];
-  __shared__ T tmp[4];
-  auto pad = [](int li) { return li + li / kItems; };
+  using L = typename ScanLocal<T>::type;
+  __shared__ L s_sum[4];
+  __shared__ T s_before[4];
   const int64_t n_eff = scan_count(n_dev, n);
   const int64_t last = scan_last_block<T>(n_eff);
   if ((int64_t)blockIdx.x > last) return;   // uniform
   const int64_t hi = n_eff > 0 ? n_eff - 1 : 0;
-  const int64_t base = (int64_t)blockIdx.x * kTile;
-  T xs[kItems];   // the tile's loads are issued first and stay in flight while the blocks
-                  // before this one are summed
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  L xs[scan_items<T>()], pre[scan_items<T>()];   // the loads are issued first and stay in flight while the blocks
+                               // before this one are summed
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
-    const int64_t i = base + (int64_t)r * kScanThreads + threadIdx.x;
-    xs[r] = ld(i < hi ? i : hi);
+  for (int r = 0; r < scan_items<T>(); ++r) {
+    const int64_t i = scan_element<T>(r);
+    const T x = ld(i < hi ? i : hi);
+    xs[r] = i < n_eff ? scan_pack(x) : (L)0;
   }
-  T before;
+  T pb = 0;
   if (fused) {
-    T pb = 0;
-    for (int64_t i = threadIdx.x; i < (int64_t)blockIdx.x; i += kScanThreads) pb += part[i];
-    block_exclusive_scan<T>(pb, tmp, before);
-  } else {
-    before = part[blockIdx.x];
-  }
+    const int64_t nb_before = blockIdx.x;
+    constexpr int kFlight = 4;
+    for (int64_t i0 = threadIdx.x; i0 < nb_before; i0 += kFlight * kScanThreads) {
+      T p[kFlight];
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
-    const int64_t i = base + (int64_t)r * kScanThreads + threadIdx.x;
-    tile[pad(r * kScanThreads + threadIdx.x)] = i < n_eff ? xs[r] : (T)0;
+      for (int u = 0; u < kFlight; ++u) {
+        const int64_t i = i0 + u * kScanThreads;
+        p[u] = part[i < nb_before ? i : 0];
+      }
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) pb += i0 + u * kScanThreads < nb_before ? p[u] : (T)0;
+    }
+    pb = wave_inclusive_scan(pb);
+  }
+  L run = 0;
+#pragma unroll
+  for (int r = 0; r < scan_items<T>(); ++r) {
+    const L x = wave_inclusive_scan(xs[r]);
+    pre[r] = run + x - xs[r];
+    run += last_lane(x);
+  }
+  if (lane == 63) {
+    s_sum[w] = run;
+    s_before[w] = pb;
   }
   __syncthreads();
-  T loc[kItems];
-  T acc = 0;
-#pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    loc[k] = acc;
-    acc += tile[pad(threadIdx.x * kItems + k)];
-  }
-  T total;
-  T pre = block_exclusive_scan<T>(acc, tmp, total) + before;
+  L local;
+  const L wave_base = sum_before<4>(s_sum, w, local);
+  const T total = ScanLocal<T>::unpack(local);
+  T before;
+  if (fused) sum_before<4>(s_before, 0, before);
+  else before = part[blockIdx.x];
   if ((int64_t)blockIdx.x == last && threadIdx.x == 0) {
     if (fused) part[nb] = before + total;
     vis.finish(before + total);
   }
-  __syncthreads();
+  constexpr int kBatch = Visit::kBatch;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) tile[pad(threadIdx.x * kItems + k)] = pre + loc[k];
-  __syncthreads();
-  const T end = before + total;   // exclusive prefix after the block
-  constexpr int kBatch = 4;
-#pragma unroll
-  for (int r0 = 0; r0 < kItems; r0 += kBatch) {
-    T p[kBatch], gap[kBatch];
+  for (int r0 = 0; r0 < scan_items<T>(); r0 += kBatch) {
     typename Visit::In in[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int li = (r0 + u) * kScanThreads + threadIdx.x;
-      const int64_t i = base + li;
-      p[u] = tile[pad(li)];
-      gap[u] = (li + 1 < kTile ? tile[pad(li + 1)] : end) - p[u];   // element i's value
-      if (i < n_eff) in[u] = vis.load(i, gap[u]);
+      const int64_t i = scan_element<T>(r0 + u);
+      if (i < n_eff) in[u] = vis.load(i, ScanLocal<T>::unpack(xs[r0 + u]));
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int64_t i = base + (r0 + u) * kScanThreads + threadIdx.x;
+      const int64_t i = scan_element<T>(r0 + u);
       if (i < n_eff) {
-        if (out) out[i] = p[u];
-        vis(i, p[u], gap[u], in[u]);
+        const T p = before + ScanLocal<T>::unpack(wave_base + pre[r0 + u]);
+        if (out) out[i] = p;
+        vis(i, p, ScanLocal<T>::unpack(xs[r0 + u]), in[u]);
       }
     }
   }
@@ -253,7 +336,7 @@ hipError_t device_scan(Load ld, int64_t n, T* out, T* part, hipStream_t s, Visit
   if (nb > 1)
     hipLaunchKernelGGL((k_scan_reduce<T, Load>), dim3((unsigned)nb), dim3(kScanThreads), 0, s, ld, n, n_dev, part);
   const bool fused = nb <= kScanFusedBlocks;
-  if (!fused) hipLaunchKernelGGL((k_scan_partials<T>), dim3(1), dim3(256), 0, s, part, nb);
+  if (!fused) hipLaunchKernelGGL((k_scan_partials<T>), dim3(1), dim3(64 * kPartialWaves), 0, s, part, nb);
   hipLaunchKernelGGL((k_scan_down<T, Load, Visit>), dim3((unsigned)nb), dim3(kScanThreads), 0, s, ld, n, n_dev, part,
                      nb, fused, out, vis);
   return hipGetLastError();
