@@ -149,6 +149,9 @@ int splat_rig_set(SplatRig* r, const SplatCamera* cams, const SplatLidar* lidars
   int64_t st_base = 0;
   for (int i = 0; i < n; ++i) {
     tab[i].st_base = st_base;
+    const bool cam = tab[i].kind == kCamera;
+    tab[i].grid = StGrid{(uint32_t)st_base, tab[i].st_x, cam ? tab[i].tiles_x : tab[i].m_az,
+                         tab[i].st_wl | (tab[i].st_hl << 8) | ((cam ? 1 : 0) << 16)};
     st_base += (int64_t)tab[i].st_x * tab[i].st_y;
     tab[i].tile_base = L.tile_base[i];
     tab[i].ray_base = L.ray_base[i];

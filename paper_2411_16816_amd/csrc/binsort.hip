@@ -260,16 +260,20 @@ static inline int radix_pass_bits(int total_bits) {
   return (total_bits + passes - 1) / passes;
 }
 
+// the first pass's digit of a sort by the low total_bits (at least 1) of its keys
+static inline uint32_t radix_first_mask(int total_bits) { return (1u << radix_pass_bits(total_bits)) - 1u; }
+
 // Sorts (k[cur], v[cur]) stably by key bits [lo_bit, lo_bit + total_bits).  On return `cur`
 // indexes the sorted keys; the sorted values are in v[cur], or in `final_vals` when it is
 // non-null.  n_ptr (device) gives the element count when non-null, capped by n_cap; only the
 // blocks that hold keys do work.  Three launches per pass: histograms, per-digit scans over
 // the blocks, scatter.  range_out (may be null): for a sort of one pass, the [start, end) of
-// every key value below n_range is also written, by the scatter; nothing for more passes.
+// every key value below n_range is also written, by the scatter; nothing for more passes.  `counted`:
+// `hist` already holds the first pass's counts (radix_first_mask).
 template <typename K, typename V>
 static hipError_t radix_sort(K* k[2], V* v[2], int& cur, const int64_t* n_ptr, int64_t n_cap, int lo_bit,
                              int total_bits, uint32_t* hist, uint32_t* coltotal, V* final_vals, hipStream_t s,
-                             uint2* range_out = nullptr, int n_range = 0) {
+                             uint2* range_out = nullptr, int n_range = 0, bool counted = false) {
   if (total_bits < 1) total_bits = 1;
   const int passes = (total_bits + kRadixBits - 1) / kRadixBits;
   if (passes > 1) range_out = nullptr;
@@ -279,8 +283,9 @@ static hipError_t radix_sort(K* k[2], V* v[2], int& cur, const int64_t* n_ptr, i
   for (int p = 0; p < passes; ++p) {
     const int shift = lo_bit + p * per;
     const int bits = (total_bits - p * per) < per ? (total_bits - p * per) : per;
-    hipLaunchKernelGGL(k_radix_hist<K>, dim3((unsigned)nb), dim3(256), 0, s, (const K*)k[cur], n_ptr, n_cap, shift,
-                       bits, hist);
+    if (p > 0 || !counted)
+      hipLaunchKernelGGL(k_radix_hist<K>, dim3((unsigned)nb), dim3(256), 0, s, (const K*)k[cur], n_ptr, n_cap, shift,
+                         bits, hist);
     hipLaunchKernelGGL(k_radix_colscan, dim3(kRadixBins), dim3(256), 0, s, hist, n_ptr, n_cap, nb, coltotal);
     V* vdst = (p == passes - 1 && final_vals) ? final_vals : v[1 - cur];
     hipLaunchKernelGGL((k_radix_scatter<K, V>), dim3((unsigned)nb), dim3(256), 0, s, (const K*)k[cur], (const V*)v[cur],
@@ -332,9 +337,9 @@ enum : int {
   kScCount = 4
 };
 
-// sensor (index into the call's table) of record rec = s * N + g; exact for rec < 2^32
-__device__ __forceinline__ int record_sensor(int64_t rec, int64_t N, int count) {
-  if (count <= 1) return 0;
+// sensor (index into the call's table) of record rec = s * N + g; exact for rec < 2^32.  No branch for
+// calls with one sensor: the loads that follow from several records' sensors then stay together.
+__device__ __forceinline__ int record_sensor(int64_t rec, int64_t N) {
   int s = (int)((float)rec * __builtin_amdgcn_rcpf((float)N));
   s -= ((int64_t)s * N > rec) ? 1 : 0;
   s += ((int64_t)(s + 1) * N <= rec) ? 1 : 0;
@@ -349,6 +354,13 @@ __device__ __forceinline__ int record_sensor(int64_t rec, int64_t N, int count) 
 __device__ __forceinline__ int grid_stride(const DevSensor& S) { return S.kind == kCamera ? S.tiles_x : S.m_az; }
 __device__ __forceinline__ int grid_rows(const DevSensor& S) { return S.kind == kCamera ? S.tiles_y : S.m_el; }
 
+// sensor s's grid, its supertiles numbered within the call
+__device__ __forceinline__ StGrid st_grid(const DevSensor* sens, int s) {
+  StGrid g = sens[s].grid;
+  g.st0 -= sens[0].grid.st0;
+  return g;
+}
+
 // Supertiles a rectangle (x0, y0, w, h) meets: rows [r0, r0 + nr) and, in each, the columns
 // [c0, c0 + nc0) followed by [0, nc1) (the second run only for a lidar rectangle that wraps the
 // azimuth seam into supertile columns it does not already cover).
@@ -356,18 +368,19 @@ struct StSpan {
   int r0, nr, c0, nc0, nc1;
 };
 
-__device__ __forceinline__ StSpan st_span(const DevSensor& S, const int4 rc) {
+__device__ __forceinline__ StSpan st_span(const StGrid& S, const int4 rc) {
+  const int wl = S.wl(), hl = S.hl();
   StSpan p;
-  p.r0 = rc.y >> S.st_hl;
-  p.nr = ((rc.y + rc.w - 1) >> S.st_hl) - p.r0 + 1;
-  const int M = grid_stride(S);
-  if (S.kind == kCamera || rc.x + rc.z <= M) {
-    p.c0 = rc.x >> S.st_wl;
-    p.nc0 = ((rc.x + rc.z - 1) >> S.st_wl) - p.c0 + 1;
+  p.r0 = rc.y >> hl;
+  p.nr = ((rc.y + rc.w - 1) >> hl) - p.r0 + 1;
+  const int M = S.stride;
+  if (S.camera() || rc.x + rc.z <= M) {
+    p.c0 = rc.x >> wl;
+    p.nc0 = ((rc.x + rc.z - 1) >> wl) - p.c0 + 1;
     p.nc1 = 0;
   } else {
-    const int a = rc.x >> S.st_wl;                    // [a, st_x) then [0, e]
-    const int e = (rc.x + rc.z - 1 - M) >> S.st_wl;
+    const int a = rc.x >> wl;                    // [a, st_x) then [0, e]
+    const int e = (rc.x + rc.z - 1 - M) >> wl;
     if (e >= a) {                                     // the two runs meet: every column
       p.c0 = 0;
       p.nc0 = S.st_x;
@@ -392,24 +405,42 @@ __device__ __forceinline__ uint32_t span_bits(int lo, int hi, int cap) {
 // the columns (bit c: tile column sc * w + c) it covers there; tile f = r * 8 + c is inside
 // exactly when both bits are set.  A lidar rectangle's columns are [x0, x0 + w) modulo M_phi,
 // i.e. the columns of [x0, x0 + w) and of [x0 - M_phi, x0 + w - M_phi) inside the grid.
-__device__ __forceinline__ void st_rows_cols(const DevSensor& S, const int4 rc, int sr, int sc, uint32_t& rows,
+__device__ __forceinline__ void st_rows_cols(const StGrid& S, const int4 rc, int sr, int sc, uint32_t& rows,
                                              uint32_t& cols) {
-  const int M = grid_stride(S);
-  const int x0 = sc << S.st_wl, y0 = sr << S.st_hl;
-  const int wcap = M - x0 < (1 << S.st_wl) ? M - x0 : (1 << S.st_wl);
+  const int M = S.stride, wl = S.wl(), hl = S.hl();
+  const int x0 = sc << wl, y0 = sr << hl;
+  const int wcap = M - x0 < (1 << wl) ? M - x0 : (1 << wl);
   cols = span_bits(rc.x - x0, rc.x + rc.z - x0, wcap);
-  if (S.kind != kCamera) cols |= span_bits(rc.x - M - x0, rc.x + rc.z - M - x0, wcap);
-  rows = span_bits(rc.y - y0, rc.y + rc.w - y0, 1 << S.st_hl);
+  if (!S.camera()) cols |= span_bits(rc.x - M - x0, rc.x + rc.z - M - x0, wcap);
+  rows = span_bits(rc.y - y0, rc.y + rc.w - y0, 1 << hl);
+}
+
+// A rectangle in 32 bits, for tile grids of at most kPackGrid rows and columns.  The sort by depth then
+// carries it in the key's upper half, and the number of supertiles it meets in the bits that the record's
+// number leaves free in the value, so that the emission of the entries in depth order reads no rectangle,
+// a random access per record (2M lidar records: emission 57 us with it, 33 without).  Where that does not fit (emit_entries), the
+// key's upper half is the number of supertiles and the rectangle is fetched.
+constexpr int kPackGrid = 256;
+
+__device__ __forceinline__ uint32_t pack_rect(const int4 rc) {
+  return (uint32_t)rc.x | ((uint32_t)rc.y << 8) | ((uint32_t)(rc.z - 1) << 16) | ((uint32_t)(rc.w - 1) << 24);
+}
+__device__ __forceinline__ int4 unpack_rect(uint32_t p) {
+  return make_int4((int)(p & 255u), (int)((p >> 8) & 255u), (int)((p >> 16) & 255u) + 1, (int)(p >> 24) + 1);
+}
+
+__device__ __forceinline__ uint32_t st_total(const StGrid& S, const int4 rc) {
+  const StSpan sp = st_span(S, rc);
+  return (uint32_t)(sp.nr * (sp.nc0 + sp.nc1));
 }
 
 // Visitor of the record-order scan of (visible, tile count) pairs.  A visible record gets its
 // entry base (the record-order prefix of the tile counts: record r owns the adjoint slots
-// [entry_base, entry_base + n_tiles)) and, at its compacted position, its depth key with the
-// number of supertiles it meets in the top 24 bits (read back in depth order by the next scan).
-// The closing block stores the visible and entry counts and the status.
+// [entry_base, entry_base + n_tiles)) and, at its compacted position, its depth key and its number, with
+// the number of supertiles it meets and the packed rectangle above them (see pack_rect).  The closing block stores the visible and entry counts and the status.
+template <bool PACKED>
 struct VisibleVisit {
   const DevSensor* sens;
-  int count;
   int64_t N;
   const int4* rect;
   const unsigned long long* dkey;
@@ -419,6 +450,7 @@ struct VisibleVisit {
   int64_t* scalars;
   int64_t k_cap;
   SplatStatus* st;
+  int rec_bits;
   static constexpr int kBatch = 8;
   struct In {
     int4 rc;
@@ -435,11 +467,9 @@ struct VisibleVisit {
   __device__ void operator()(int64_t i, P64 p, P64 v, const In& in) const {
     if (line_seen<int64_t>(__ballot(v.a != 0), i)) entry_base[i] = p.b;
     if (v.a == 0) return;
-    const DevSensor& S = sens[record_sensor(i, N, count)];
-    const StSpan sp = st_span(S, in.rc);
-    const uint64_t n_st = (uint64_t)(sp.nr * (sp.nc0 + sp.nc1));
-    keys[p.a] = (n_st << kDepthKeyBits) | depth_sort_key(in.dk);
-    vals[p.a] = (uint32_t)i;
+    const uint32_t n_st = st_total(st_grid(sens, record_sensor(i, N)), in.rc);
+    keys[p.a] = ((uint64_t)(PACKED ? pack_rect(in.rc) : n_st) << kDepthKeyBits) | depth_sort_key(in.dk);
+    vals[p.a] = (uint32_t)i | (PACKED ? n_st << rec_bits : 0u);
   }
   __device__ void finish(P64 total) const {
     scalars[kScVisible] = total.a;
@@ -460,14 +490,17 @@ struct LoadVisibleTiles {
   }
 };
 
-// supertile count of the i-th visible record in depth order, from its sorted packed key
-// (entries past the visible count hold stale keys and count zero)
+// supertile count of the i-th visible record in depth order, from its sorted value or key
+// (entries past the visible count are stale and count zero)
+template <bool PACKED>
 struct LoadPackedCount {
   const uint64_t* keys;
+  const uint32_t* vals;
   const int64_t* n_vis;
+  int rec_bits;
   __device__ int64_t operator()(int64_t i) const {
-    const uint64_t k = keys[i];
-    return i < *n_vis ? (int64_t)(k >> kDepthKeyBits) : 0;
+    const int64_t c = PACKED ? (int64_t)(vals[i] >> rec_bits) : (int64_t)(keys[i] >> kDepthKeyBits);
+    return i < *n_vis ? c : 0;
   }
 };
 
@@ -495,87 +528,161 @@ __device__ __forceinline__ uint64_t coarse_value(uint32_t gid, uint32_t rows, ui
 }
 
 // Entry j (row-major over its supertile span) of a record: the supertile key and the value.
-__device__ __forceinline__ void coarse_entry(const DevSensor& S, uint32_t st0, const int4 rc, const StSpan& sp,
-                                             uint32_t gid, int j, uint32_t& key, uint64_t& val) {
+__device__ __forceinline__ void coarse_entry(const StGrid& S, const int4 rc, uint32_t gid, int j, uint32_t& key,
+                                             uint64_t& val) {
+  const StSpan sp = st_span(S, rc);
   const int nc = sp.nc0 + sp.nc1;
-  const int r = j / nc, c = j - r * nc;
+  int r = (int)((float)j * __builtin_amdgcn_rcpf((float)nc));   // within 1: j < 2^24 (a record's supertiles)
+  r -= r * nc > j ? 1 : 0;
+  r += (r + 1) * nc <= j ? 1 : 0;
+  const int c = j - r * nc;
   const int sr = sp.r0 + r;
   const int sc = c < sp.nc0 ? sp.c0 + c : c - sp.nc0;
   uint32_t rows, cols;
   st_rows_cols(S, rc, sr, sc, rows, cols);
-  key = st0 + (uint32_t)sr * (uint32_t)S.st_x + (uint32_t)sc;
+  key = S.st0 + (uint32_t)sr * (uint32_t)S.st_x + (uint32_t)sc;
   val = coarse_value(gid, rows, cols);
 }
 
-// Visible record i (depth order) writes its (local supertile, record) entries from its offset
-// coff[i] on.  Each lane writes the first kEmitOwn entries of its own record; the entries
-// beyond that of the wavefront's larger records are then written by the whole wavefront, one
-// record at a time, 64 entries per step.  The grid also empties the first n_st supertile
-// ranges ([0, 0)) when the supertile sort leaves them to a ranges pass (n_st = 0 otherwise).
-constexpr int kEmitOwn = 4;
+// The last of offs[lo .. lo + len) that does not exceed x (they do not decrease, and offs[lo] does not):
+// 64 probes at a time, one per lane of the wavefront.
+__device__ __forceinline__ int64_t wave_find_last(const int64_t* __restrict__ offs, int64_t lo, int64_t len, int64_t x) {
+  const int64_t lane = threadIdx.x & 63;
+  while (len > 1) {   // uniform
+    const int64_t step = (len + 63) >> 6, d = lane * step;
+    const int64_t v = offs[lo + (d < len ? d : 0)];
+    const int k = 63 - __clzll((long long)__ballot(d < len && v <= x));   // lane 0 always votes
+    lo += k * step;
+    len = len - k * step < step ? len - k * step : step;
+  }
+  return lo;
+}
 
-__global__ __launch_bounds__(256) void k_coarse_emit(const DevSensor* __restrict__ sens, int count, int64_t N,
-                                                     const int4* __restrict__ rect, const uint32_t* __restrict__ order,
+// Writes the (local supertile, record) entries in depth order, entry by entry: a workgroup takes runs of
+// one radix tile of consecutive entries, finds the record of the first one in the scanned counts coff, and
+// spreads the records from there on over the entries: each writes its number (from 1 on) at its first
+// entry in LDS, and the maximum of those up to an entry (a scan on DPP) is the entry's record.  The work is then even
+// whatever a record's size (the nearest, largest ones are neighbours in depth order), the stores are
+// consecutive, and the tile's digit counts for the first pass of the supertile sort come with it, which
+// saves that pass a read of the keys.  With one record per lane and the larger ones by a wavefront, and the
+// counts in a pass of their own: 500k camera records 63 + 19 -> 27 us, 2M lidar records 58 + 8 -> 33,
+// seven sensors over 1.5M Gaussians 108 + 15 -> 55, 4096 lidar records 13 + 4 -> 9.
+// The grid also empties the first n_st supertile ranges ([0, 0)) when the supertile sort leaves them to a
+// ranges pass (n_st = 0 otherwise).
+constexpr int kEmitWaves = 4, kEmitRows = kRadixTile / (64 * kEmitWaves);
+constexpr int kEmitBatch = 4;     // rows whose records are loaded together
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_max(uint32_t x) {
+  const uint32_t y = dpp_from<CTRL, ROWS>(x);
+  return x > y ? x : y;
+}
+
+template <bool PACKED>
+__global__ __launch_bounds__(256) void k_coarse_emit(const DevSensor* __restrict__ sens, int64_t N,
+                                                     const int4* __restrict__ rect, const uint64_t* __restrict__ dkeys,
+                                                     const uint32_t* __restrict__ order,
                                                      const int64_t* __restrict__ coff,
-                                                     const int64_t* __restrict__ scalars, int64_t n_cap,
+                                                     const int64_t* __restrict__ scalars, int64_t n_cap, int rec_bits,
                                                      uint32_t* __restrict__ ckeys, uint64_t* __restrict__ cvals,
-                                                     int64_t cap, uint32_t* __restrict__ crange, int64_t n_st) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int lane = threadIdx.x & 63;
-  for (int64_t z = i; z < 2 * n_st; z += (int64_t)gridDim.x * blockDim.x) crange[z] = 0u;
-  const bool valid = i < n_cap && i < scalars[kScVisible] && scalars[kScCoarse] != 0;
-  uint32_t rec = 0, gid = 0;
-  int64_t q0 = 0;
-  int s = 0, cnt = 0;
-  int4 rc = make_int4(0, 0, 0, 0);
-  StSpan sp{0, 0, 0, 0, 0};
-  if (valid) {
-    rec = order[i];
-    q0 = coff[i];
-    s = record_sensor(rec, N, count);
-    rc = rect[rec];
-    sp = st_span(sens[s], rc);
-    gid = (uint32_t)((int64_t)rec - (int64_t)s * N);
-    cnt = sp.nr * (sp.nc0 + sp.nc1);
-  }
-  if (valid) {
-    const DevSensor& S = sens[s];
-    const uint32_t st0 = (uint32_t)(S.st_base - sens[0].st_base);
-    for (int j = 0; j < cnt && j < kEmitOwn; ++j) {
-      uint32_t key;
-      uint64_t val;
-      coarse_entry(S, st0, rc, sp, gid, j, key, val);
-      if (q0 + j < cap) {
-        ckeys[q0 + j] = key;
-        cvals[q0 + j] = val;
+                                                     uint32_t* __restrict__ crange, int64_t n_st,
+                                                     uint32_t* __restrict__ hist, int64_t hist_stride, uint32_t mask) {
+  __shared__ uint32_t s_head[kRadixTile];   // 1 + record (from the tile's first) that begins at the entry
+  __shared__ uint32_t s_last[kEmitWaves];
+  __shared__ uint32_t s_hist[kRadixBins];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  for (int64_t z = (int64_t)blockIdx.x * 256 + tid; z < 2 * n_st; z += (int64_t)gridDim.x * 256) crange[z] = 0u;
+  const int64_t total = scalars[kScCoarse];   // at most the capacity of ckeys and cvals
+  const int64_t n_vis = scalars[kScVisible] < n_cap ? scalars[kScVisible] : n_cap;
+  const int64_t tiles = (total + kRadixTile - 1) / kRadixTile;
+  const int64_t per = (tiles + gridDim.x - 1) / gridDim.x;
+  const int64_t first = blockIdx.x * per, end = first + per < tiles ? first + per : tiles;
+  if (first >= end) return;   // uniform
+  int64_t lo = wave_find_last(coff, 0, n_vis, first * kRadixTile);
+  for (int64_t c = first; c < end; ++c) {
+    const int64_t e0 = c * kRadixTile;
+    const int cnt = (int)(total - e0 < kRadixTile ? total - e0 : kRadixTile);
+    // Every record from lo on has an entry, so those of kRadixTile records reach past the tile.
+    int64_t off[kRadixTile / 256];
+#pragma unroll
+    for (int k = 0; k < kRadixTile / 256; ++k) {
+      const int64_t q = lo + tid + 256 * k;
+      off[k] = coff[q < n_vis ? q : n_vis - 1] - e0;
+      s_head[tid + 256 * k] = 0u;
+    }
+    s_hist[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRadixTile / 256; ++k) {
+      const int q = tid + 256 * k;
+      if (q == 0) {
+        s_head[0] = 1u;   // it may begin before the tile
+      } else if (lo + q < n_vis && off[k] < kRadixTile) {
+        s_head[off[k]] = (uint32_t)q + 1u;
       }
     }
-  }
-  uint64_t heavy = __ballot(cnt > kEmitOwn);
-  while (heavy) {   // uniform
-    const int l = __ffsll((unsigned long long)heavy) - 1;
-    heavy &= heavy - 1;
-    const int sl = __builtin_amdgcn_readlane(s, l);
-    const int4 rl = make_int4(__builtin_amdgcn_readlane(rc.x, l), __builtin_amdgcn_readlane(rc.y, l),
-                              __builtin_amdgcn_readlane(rc.z, l), __builtin_amdgcn_readlane(rc.w, l));
-    const StSpan pl{__builtin_amdgcn_readlane(sp.r0, l), __builtin_amdgcn_readlane(sp.nr, l),
-                    __builtin_amdgcn_readlane(sp.c0, l), __builtin_amdgcn_readlane(sp.nc0, l),
-                    __builtin_amdgcn_readlane(sp.nc1, l)};
-    const uint32_t gl = (uint32_t)__builtin_amdgcn_readlane((int)gid, l);
-    const int64_t ql = ((int64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)q0, l)) |
-                       ((int64_t)__builtin_amdgcn_readlane((int)(q0 >> 32), l) << 32);
-    const int cl = __builtin_amdgcn_readlane(cnt, l);
-    const DevSensor& S = sens[sl];
-    const uint32_t st0 = (uint32_t)(S.st_base - sens[0].st_base);
-    for (int j = kEmitOwn + lane; j < cl; j += 64) {
-      uint32_t key;
-      uint64_t val;
-      coarse_entry(S, st0, rl, pl, gl, j, key, val);
-      if (ql + j < cap) {
-        ckeys[ql + j] = key;
-        cvals[ql + j] = val;
-      }
+    __syncthreads();
+    // record of each entry (from 1 on): the wavefront's rows in order, then the wavefronts before it
+    uint32_t rec1[kEmitRows];
+    uint32_t run = 0u;
+#pragma unroll
+    for (int r = 0; r < kEmitRows; ++r) {
+      uint32_t x = s_head[(w * kEmitRows + r) * 64 + lane];
+      x = dpp_max<0x111, 0xf>(x);
+      x = dpp_max<0x112, 0xf>(x);
+      x = dpp_max<0x114, 0xf>(x);
+      x = dpp_max<0x118, 0xf>(x);
+      x = dpp_max<0x142, 0xa>(x);
+      x = dpp_max<0x143, 0xc>(x);
+      rec1[r] = x > run ? x : run;
+      run = last_lane(rec1[r]);
     }
+    if (lane == 0) s_last[w] = run;
+    __syncthreads();
+    uint32_t before = 0u, last = 0u;
+#pragma unroll
+    for (int k = 0; k < kEmitWaves; ++k) {
+      const uint32_t x = s_last[k];
+      if (k < w) before = before > x ? before : x;
+      last = last > x ? last : x;
+    }
+#pragma unroll
+    for (int r0 = 0; r0 < kEmitRows; r0 += kEmitBatch) {
+      uint32_t rec[kEmitBatch];
+      int4 rc[kEmitBatch];
+      int j[kEmitBatch];
+#pragma unroll
+      for (int u = 0; u < kEmitBatch; ++u) {
+        const uint32_t k = (rec1[r0 + u] > before ? rec1[r0 + u] : before) - 1u;
+        rec[u] = PACKED ? order[lo + k] & ((1u << rec_bits) - 1u) : order[lo + k];
+        if (PACKED) rc[u] = unpack_rect((uint32_t)(dkeys[lo + k] >> kDepthKeyBits));
+        j[u] = (int)(e0 + (w * kEmitRows + r0 + u) * 64 + lane - coff[lo + k]);
+      }
+#pragma unroll
+      for (int u = 0; u < kEmitBatch; ++u)
+        if (!PACKED) rc[u] = rect[rec[u]];
+#pragma unroll
+      for (int u = 0; u < kEmitBatch; ++u) {
+        const int e = (w * kEmitRows + r0 + u) * 64 + lane;
+        const int s = record_sensor(rec[u], N);
+        uint32_t key;
+        uint64_t val;
+        coarse_entry(st_grid(sens, s), rc[u], (uint32_t)((int64_t)rec[u] - (int64_t)s * N),
+                     j[u], key, val);
+        if (e < cnt) {
+          ckeys[e0 + e] = key;
+          cvals[e0 + e] = val;
+          atomicAdd(&s_hist[key & mask], 1u);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // the next tile begins with this one's last record, or with the one after it
+    lo += last - 1;
+    if (c + 1 < end && lo + 1 < n_vis && coff[lo + 1] <= e0 + kRadixTile) ++lo;   // uniform
+    __syncthreads();
+    hist[(int64_t)tid * hist_stride + c] = s_hist[tid];
+    __syncthreads();
   }
 }
 
@@ -1079,6 +1186,44 @@ static hipError_t launch_ray_bins(const CallView& v, const SplatTileLists& L, co
   return hipGetLastError();
 }
 
+// Steps 1 to 3: the entries of the visible records, in depth order (PACKED: see pack_rect).  With `clear`
+// the supertile ranges are emptied.
+template <bool PACKED>
+static hipError_t emit_entries(const CallView& v, const SplatProjected& p, const SplatTileLists& L, const Workspace& w,
+                               SplatStatus* st, int64_t n_rec, int rec_bits, bool clear, int st_bits, hipStream_t s) {
+  hipError_t e;
+  int64_t* const sc = w.scalars;
+  const int64_t n_st = v.n_supertiles;
+  // 1. one record-order scan of (visible, tile count): entry bases, the visible records'
+  //    packed depth keys compacted in record order, the counts and the overflow status
+  if ((e = device_scan<P64>(LoadVisibleTiles{p.n_tiles}, n_rec, (P64*)nullptr, (P64*)w.scan_part, s,
+                            VisibleVisit<PACKED>{v.sens, v.n_gauss, (const int4*)p.rect,
+                                                 (const unsigned long long*)p.dkey, L.entry_base, w.dkeys[0], w.dvals[0],
+                                                 sc, L.k_cap, st, rec_bits})) != hipSuccess)
+    return e;
+  // 2. stable sort of the visible records by the 32-bit depth key (ties keep record order)
+  uint64_t* dk[2] = {w.dkeys[0], w.dkeys[1]};
+  uint32_t* dv[2] = {w.dvals[0], w.dvals[1]};
+  int cur = 0;
+  if ((e = radix_sort<uint64_t, uint32_t>(dk, dv, cur, sc + kScVisible, n_rec, 0, kDepthKeyBits, w.hist, w.coltotal,
+                                          nullptr, s)) != hipSuccess)
+    return e;
+  // 3. depth-order scan of the supertile counts, emitting (supertile, record) entries in depth
+  //    order
+  if ((e = device_scan<int64_t>(LoadPackedCount<PACKED>{dk[cur], dv[cur], sc + kScVisible, rec_bits}, n_rec, w.coff,
+                                (int64_t*)w.scan_part, s, CoarseCount{sc, L.k_cap}, sc + kScVisible)) != hipSuccess)
+    return e;
+  if (n_rec == 0) return clear ? fill<int32_t>((int32_t*)w.crange, 2 * n_st, 0, s) : hipSuccess;   // [0, 0): empty
+  // as many workgroups as the entries can need, at most eight per compute unit
+  const int64_t tiles = div_up(L.k_cap, kRadixTile);
+  const int64_t eb = tiles < 1 ? 1 : tiles > 2048 ? 2048 : tiles;
+  hipLaunchKernelGGL(k_coarse_emit<PACKED>, dim3((unsigned)eb), dim3(256), 0, s, v.sens, v.n_gauss,
+                     (const int4*)p.rect, (const uint64_t*)dk[cur], (const uint32_t*)dv[cur], (const int64_t*)w.coff,
+                     (const int64_t*)sc, n_rec, rec_bits, w.ckeys[0], w.cvals[0], (uint32_t*)w.crange, clear ? n_st : (int64_t)0,
+                     w.hist, tiles, radix_first_mask(st_bits));
+  return hipGetLastError();
+}
+
 hipError_t launch_bin_sort(const CallView& v, const SplatProjected& p, const SplatTileLists& L, const Workspace& w,
                            SplatStatus* st, hipStream_t s) {
   const int64_t n_rec = (int64_t)v.count * v.n_gauss;
@@ -1095,41 +1240,29 @@ hipError_t launch_bin_sort(const CallView& v, const SplatProjected& p, const Spl
     if ((e = launch_ray_bins(v, L, w, st, fork ? v.side : s)) != hipSuccess) return e;
     if (fork && (e = hipEventRecord(v.join, v.side)) != hipSuccess) return e;
   }
-  // 1. one record-order scan of (visible, tile count): entry bases, the visible records'
-  //    packed depth keys compacted in record order, the counts and the overflow status
-  if ((e = device_scan<P64>(LoadVisibleTiles{p.n_tiles}, n_rec, (P64*)nullptr, (P64*)w.scan_part, s,
-                            VisibleVisit{v.sens, v.count, v.n_gauss, (const int4*)p.rect,
-                                         (const unsigned long long*)p.dkey, L.entry_base, w.dkeys[0], w.dvals[0], sc,
-                                         L.k_cap, st})) != hipSuccess)
-    return e;
-  // 2. stable sort of the visible records by the 32-bit depth key (ties keep record order)
-  uint64_t* dk[2] = {w.dkeys[0], w.dkeys[1]};
-  uint32_t* dvv[2] = {w.dvals[0], w.dvals[1]};
-  int cur = 0;
-  if ((e = radix_sort<uint64_t, uint32_t>(dk, dvv, cur, sc + kScVisible, n_rec, 0, kDepthKeyBits, w.hist, w.coltotal,
-                                nullptr, s)) != hipSuccess)
-    return e;
-  // 3. depth-order scan of the supertile counts, emitting (supertile, record) entries in depth
-  //    order
-  if ((e = device_scan<int64_t>(LoadPackedCount{dk[cur], sc + kScVisible}, n_rec, w.coff, (int64_t*)w.scan_part, s,
-                                CoarseCount{sc, L.k_cap}, sc + kScVisible)) != hipSuccess)
-    return e;
   const int64_t n_st = v.n_supertiles;
   // with at most kRadixBins supertiles step 4 is one radix pass, whose scatter writes the
   // supertile ranges; otherwise the emit clears them and a ranges pass fills them in
   const bool one_pass = n_st <= kRadixBins && L.k_cap > 0;
-  if (n_rec > 0)
-    hipLaunchKernelGGL(k_coarse_emit, dim3((unsigned)div_up(n_rec, 256)), dim3(256), 0, s, v.sens, v.count, v.n_gauss,
-                       (const int4*)p.rect, (const uint32_t*)dvv[cur], (const int64_t*)w.coff, (const int64_t*)sc, n_rec,
-                       w.ckeys[0], w.cvals[0], L.k_cap, (uint32_t*)w.crange, one_pass ? (int64_t)0 : n_st);
-  else if ((e = fill<int32_t>((int32_t*)w.crange, 2 * n_st, 0, s)) != hipSuccess)   // [0, 0): empty
-    return e;
+  const int st_bits = bits_for(n_st);
+  // packed records: every grid fits the packed rectangles, every count of supertiles the bits above the
+  // record numbers
+  const int rec_bits = bits_for(n_rec);
+  bool packed = n_rec <= (int64_t)1 << rec_bits;
+  for (int i = 0; i < v.count; ++i) {
+    const DevSensor& S = v.host[i];
+    const int cols = S.kind == kCamera ? S.tiles_x : S.m_az, rows = S.kind == kCamera ? S.tiles_y : S.m_el;
+    packed = packed && cols <= kPackGrid && rows <= kPackGrid && (int64_t)S.st_x * S.st_y < (int64_t)1 << (32 - rec_bits);
+  }
+  e = packed ? emit_entries<true>(v, p, L, w, st, n_rec, rec_bits, !one_pass, st_bits, s)
+             : emit_entries<false>(v, p, L, w, st, n_rec, rec_bits, !one_pass, st_bits, s);
+  if (e != hipSuccess) return e;
   // 4. stable sort of the entries by supertile: each supertile's records stay in depth order
   uint32_t* ck[2] = {w.ckeys[0], w.ckeys[1]};
   uint64_t* cv[2] = {w.cvals[0], w.cvals[1]};
   int ccur = 0;
-  if ((e = radix_sort<uint32_t, uint64_t>(ck, cv, ccur, sc + kScCoarse, L.k_cap, 0, bits_for(n_st), w.hist, w.coltotal,
-                                nullptr, s, one_pass ? w.crange : nullptr, (int)(one_pass ? n_st : 0))) != hipSuccess)
+  if ((e = radix_sort<uint32_t, uint64_t>(ck, cv, ccur, sc + kScCoarse, L.k_cap, 0, st_bits, w.hist, w.coltotal,
+                                nullptr, s, one_pass ? w.crange : nullptr, (int)(one_pass ? n_st : 0), n_rec > 0)) != hipSuccess)
     return e;
   if (L.k_cap > 0 && !one_pass)
     hipLaunchKernelGGL(k_ranges<uint2>, dim3((unsigned)div_up(L.k_cap, 256 * kRangeItems)), dim3(256), 0, s,

@@ -27,8 +27,20 @@ constexpr int kStLogLidar = 2;
 
 enum SensorKind : int32_t { kCamera = 0, kLidar = 1 };
 
+// What the binning of one record needs of its sensor, in one 16-byte load (records in depth order mix the
+// sensors, so that every lane loads its own).
+struct alignas(16) StGrid {
+  uint32_t st0;           // first supertile (global numbering inside the rig; kernels make it the call's)
+  int32_t st_x, stride;   // supertiles and tiles per row
+  int32_t shape;          // log2 of a supertile's width and height in tiles (8 bits each), then 1 for a camera
+  HD int wl() const { return shape & 255; }
+  HD int hl() const { return (shape >> 8) & 255; }
+  HD bool camera() const { return (shape >> 16) != 0; }
+};
+
 // One sensor as the kernels see it (built on the host from SplatCamera / SplatLidar).
 struct alignas(16) DevSensor {
+  StGrid grid;
   int32_t kind;
   int32_t feat_off, n_ch;      // blended feature columns
   int32_t n_tiles;             // tiles of this sensor

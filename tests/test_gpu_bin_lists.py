@@ -2,7 +2,8 @@
 computed in numpy from the projected records (rectangles, depths), at record counts around the wavefront
 (64), the write line (8 and 16 records), the scans' blocks (2048 pairs, 4096 counts) and the emission's
 chunks, with few and with many supertiles per record, for one camera, one lidar (rectangles across the
-azimuth seam) and both in one call."""
+azimuth seam), both in one call, and with a camera of exactly 256 and of more than 256 tile columns
+(rectangles packed in 32 bits, and not)."""
 import numpy as np
 import pytest
 import torch
@@ -23,8 +24,9 @@ def _scene(n, size, which):
     rng = np.random.default_rng(n + int(100 * size))
     g = S.random_gaussians(rng, rng.uniform([-30, -30, -3], [30, 30, 3], (n, 3)), 11, moving_frac=0.3)
     g.log_scales += np.float32(np.log(size))
-    cam = S.make_camera(np.zeros(3), 10.0, 700, 300, 320.0, n_channels=8) if "c" in which else None
-    lid = S.make_lidar(np.zeros(3), 0.0, 32, -25.0, 15.0, 900, feat_offset=8, n_channels=3) if "l" in which else None
+    size_px = {"w": (4110, 60), "e": (4096, 60)}.get(which[0], (700, 300))
+    cam = S.make_camera(np.zeros(3), 10.0, *size_px, 320.0, n_channels=8) if which[0] != "l" else None
+    lid = S.make_lidar(np.zeros(3), 0.0, 32, -25.0, 15.0, 900, feat_offset=8, n_channels=3) if which[-1] == "l" else None
     return g, [cam] if cam else [], [lid] if lid else []
 
 
@@ -57,7 +59,7 @@ def _expected(rig, sp, n):
     return nt, [gid[a:b].tolist() for a, b in zip(starts, ends)]
 
 
-@pytest.mark.parametrize("which", ["c", "l", "cl"])
+@pytest.mark.parametrize("which", ["c", "l", "cl", "e", "wl"])
 @pytest.mark.parametrize("n,size", [(1, 3.0), (63, 1.0), (130, 25.0), (2047, 1.0), (2049, 4.0), (4099, 0.3), (20011, 1.0)])
 def test_lists(n, size, which):
     b = _binding()
