@@ -1,9 +1,10 @@
 """Binning alone, whole: entry numbers and every tile's list, bit for bit against the same integers
 computed in numpy from the projected records (rectangles, depths), at record counts around the wavefront
 (64), the write line (8 and 16 records), the scans' blocks (2048 pairs, 4096 counts) and the emission's
-chunks, with few and with many supertiles per record, for one camera, one lidar (rectangles across the
-azimuth seam), both in one call, and with a camera of exactly 256 and of more than 256 tile columns
-(rectangles packed in 32 bits, and not)."""
+chunks, on both sides of the sort in one workgroup (8192 records), with few and with many supertiles per
+record, with equal depths, for one camera, one lidar (rectangles across the azimuth seam), both in one
+call, and with a camera of exactly 256 and of more than 256 tile columns (rectangles packed in 32 bits,
+and not)."""
 import numpy as np
 import pytest
 import torch
@@ -59,11 +60,28 @@ def _expected(rig, sp, n):
     return nt, [gid[a:b].tolist() for a, b in zip(starts, ends)]
 
 
+def _tied(g):
+    """A third of the Gaussians in the places of others: equal depths, listed in the order of their ids."""
+    n = len(g.means)
+    g.means[: n // 3] = g.means[n - n // 3:][::-1]
+
+
+@pytest.mark.parametrize("n,which", [(600, "c"), (2048, "c"), (4096, "l"), (8192, "c"), (8193, "l"), (4096, "cl"), (8192, "w")])
+def test_equal_depths(n, which):
+    b = _binding()
+    g, cams, lids = _scene(n, 2.0, which)
+    _tied(g)
+    _check_lists(b, g, cams, lids, n)
+
+
 @pytest.mark.parametrize("which", ["c", "l", "cl", "e", "wl"])
 @pytest.mark.parametrize("n,size", [(1, 3.0), (63, 1.0), (130, 25.0), (2047, 1.0), (2049, 4.0), (4099, 0.3), (20011, 1.0)])
 def test_lists(n, size, which):
-    b = _binding()
     g, cams, lids = _scene(n, size, which)
+    _check_lists(_binding(), g, cams, lids, n)
+
+
+def _check_lists(b, g, cams, lids, n):
     rig = b.Rig(cams, lids)
     G = b.GaussTensors.from_numpy(g)
     sp = b.SensorPass(rig, 0, len(rig.sensors), n, 1, batched=len(rig.sensors) > 1)
