@@ -328,7 +328,9 @@ int splat_rasterize_fwd_lidar(const SplatGaussians* g, const SplatRig* rig, int3
  * per-kind kernels instead (no queue; work holds lidar chunks only, as in the per-kind call).
  * Lists need ray_order (if any lidar), ray_range, work and n_work.  Results are bit-identical
  * to the per-sensor calls (BOX support).  Gradients agree with the per-sensor calls to float
- * rounding: a workgroup adds its wavefronts' partial sums in LDS in scheduling order. */
+ * rounding: the form of the adjoint's walk goes by the whole call's work items.  A call repeated gives
+ * the same gradient bits, except where work items add atomically: in lidar tiles of more than 256 rays,
+ * beyond the adjoint row limit, and in the time offsets of the cameras. */
 int splat_project(const SplatGaussians* g, const SplatRig* rig, int32_t first, int32_t count,
                   const SplatProjected* out, SplatStatus* status, void* stream);
 int splat_bin_sort(const SplatRig* rig, int32_t first, int32_t count, int64_t n_gaussians,

@@ -452,17 +452,19 @@ constexpr int kBwdLanes = 128;
 constexpr int kRpl = kBlock / kBwdLanes;   // rays per lane
 constexpr int kBwdBatch = 64;              // Gaussians staged per batch (one per lane of wavefront 0)
 
-template <int CMAX>
+// A batch's sums, one set for every two wavefronts of the group: two additions into a cleared word give
+// the same bits in either order, more of them would not.
+template <int CMAX, int PAIRS>
 struct BwdSeg {
   float4 rec[kBwdBatch * rec4(CMAX)];
-  float acc[BwdShape<CMAX>::V][kBwdBatch];
+  float acc[PAIRS][BwdShape<CMAX>::V][kBwdBatch];
   int used[kBwdBatch];
 };
 
-template <int CMAX, int SEG = 1>
+template <int CMAX, int P = kRpl, int SEG = 1>
 struct BwdSmem {
   static constexpr int kCmax = CMAX;   // the launch's channel bucket: sets the gradient row stride
-  BwdSeg<CMAX> seg[SEG];
+  BwdSeg<CMAX, kBlock / P / 128> seg[SEG];
   float state[SEG][3][SEG > 1 ? kBlock : 1];   // per segment and ray: product of 1 - alpha, blends
   int maxlast;
   float toff;   // the item's time-offset gradient, summed over its wavefronts
@@ -499,7 +501,9 @@ __device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, in
   const int seg = SEG == 1 ? 0 : (int)(threadIdx.x / kLanes);
   auto& sm = smw.seg[seg];
   static_assert(SH::V <= 64, "channels");
-  static_assert(sizeof(sm.acc) / sizeof(sm.acc[0]) >= SH::V, "accumulator rows");
+  constexpr int kPairs = kLanes / 128;   // of wavefronts, each with its own sums
+  static_assert(sizeof(sm.acc) / sizeof(sm.acc[0]) == kPairs, "accumulators");
+  static_assert(sizeof(sm.acc[0]) / sizeof(sm.acc[0][0]) >= SH::V, "accumulator rows");
   static_assert(sizeof(sm.rec) / sizeof(sm.rec[0]) >= kBwdBatch * R4, "record staging");
   static_assert(SEG == 1 || sizeof(smw.state) / sizeof(smw.state[0]) >= SEG, "segment states");
   auto& s_acc = sm.acc;
@@ -537,7 +541,9 @@ __device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, in
     smw.maxlast = 0;
     smw.toff = 0.f;
   }
-  for (int k = tid; k < SH::V * kBwdBatch; k += kLanes) (&s_acc[0][0])[k] = 0.f;
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u)
+    for (int k = tid; k < SH::V * kBwdBatch; k += kLanes) (&s_acc[u][0][0])[k] = 0.f;
   if (tid < kBwdBatch) s_used[tid] = 0;
   __syncthreads();
   int my_last = last_l[0];
@@ -760,11 +766,17 @@ __device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, in
         for (int k = 0; k < VR; ++k) u[k] = v[k < kNV - 1 ? k : k + 1];
         r_own = wave_reduce_scatter<VR>(u);
       }
-      if (my_store) atomicAdd(&s_acc[my_idx][j], r_own);
+      if (my_store) atomicAdd(&s_acc[kPairs == 1 ? 0 : wave >> 1][my_idx][j], r_own);
       if (lane == 0) s_used[j] = 1;
     }
     __syncthreads();
     if (tid < nb && s_used[tid]) {
+      auto sum = [&](int k) {   // value k of the Gaussian, in a fixed order
+        float x = s_acc[0][k][tid];
+#pragma unroll
+        for (int u = 1; u < kPairs; ++u) x += s_acc[u][k][tid];
+        return x;
+      };
       const int64_t rec = my_rec;
       const int64_t g = rec - (int64_t)c[0].s * a.N;
       b.rflag[rec] = 1;   // idempotent: every writer stores the same byte
@@ -776,21 +788,23 @@ __device__ __forceinline__ void bwd_item(const RasterArgs& a, const BwdIn& b, in
         for (int q = 0; q < SW / 4; ++q) {
           float x[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) x[u] = (4 * q + u < SH::V) ? s_acc[4 * q + u][tid] * value_scale(4 * q + u) : 0.f;
+          for (int u = 0; u < 4; ++u) x[u] = (4 * q + u < SH::V) ? sum(4 * q + u) * value_scale(4 * q + u) : 0.f;
           row[q] = make_float4(x[0], x[1], x[2], x[3]);
         }
         b.flags[p] = 1;
       } else {
         float* gp = b.g2d + rec * kNV;
 #pragma unroll
-        for (int k = 0; k < kNV; ++k) atomicAdd(gp + k, s_acc[k][tid] * value_scale(k));
+        for (int k = 0; k < kNV; ++k) atomicAdd(gp + k, sum(k) * value_scale(k));
         float* fp = b.dfeat + g * a.c_total + S.feat_off;
 #pragma unroll
         for (int k = 0; k < CMAX; ++k)
-          if (k < c[0].C) atomicAdd(fp + k, s_acc[kNV + k][tid]);
+          if (k < c[0].C) atomicAdd(fp + k, sum(kNV + k));
       }
 #pragma unroll
-      for (int k = 0; k < SH::V; ++k) s_acc[k][tid] = 0.f;
+      for (int u = 0; u < kPairs; ++u)
+#pragma unroll
+        for (int k = 0; k < SH::V; ++k) s_acc[u][k][tid] = 0.f;
       s_used[tid] = 0;
     }
     __syncthreads();
@@ -825,7 +839,7 @@ enum : int { kItemsCamera = 1, kItemsLidar = 2, kItemsBoth = 3, kItemsGrouped = 
 // list in SEG segments.
 template <int CMC, int CML, int KINDS, int P, int SEG>
 __global__ __launch_bounds__(kBlock / P * SEG) void k_raster_bwd_seg(RasterArgs a, BwdIn b) {
-  __shared__ BwdSmem<cmax_max(CMC, CML), SEG> sm;
+  __shared__ BwdSmem<cmax_max(CMC, CML), P, SEG> sm;
   int2 w = make_int2((int)blockIdx.x, 0);
   if (a.n_work) {   // uniform: not a camera call
     if ((int64_t)blockIdx.x >= (int64_t)a.n_work[0]) return;
@@ -979,7 +993,7 @@ static int64_t item_estimate(const CallView& v) {
 // The segmented adjoint takes calls whose items do not fill the chip: up to one item per compute unit
 // with 8 segments x 128 lanes, up to two with 2 x 256.  Kernel times, segmented against one walk per
 // item: camera 157 x 93 (60 tiles) 163 against 338 us, 320 x 180 (240) 112 / 227, lidar 32 x 1024
-// (128) 100 / 193, camera 480 x 270 (510) 117 / 145, lidar 128 x 1024 (512) 132 / 197; at 920 camera
+// (128) 100 / 193, camera 480 x 270 (510) 117 / 145, lidar 128 x 1024 (512) 134 / 197; at 920 camera
 // tiles the extra pass costs more than it gives (256 / 227).  BOX calls of at most 16 channels only:
 // wider rows spill (213 registers at 32 channels, against 128 for 1024 lanes).
 constexpr int kSegChannels = 16;
