@@ -54,8 +54,15 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
 // instructions: 3.0e-7), of which -1.7e-8 is a bias that sums over many pixels would collect.  With
 // the hh products, which align, in an accumulator of their own the error is 9.5e-8 and the bias below
 // 1e-9.  Where the registers do not allow that, half of the terms are contracted negated and
-// subtracted, so that the bias cancels.  Infinities, NaN and magnitudes near the type's limits do not
-// split; the kernels find them and contract those outputs in plain FP32.
+// subtracted, so that the bias cancels.
+//
+// Operands are split scaled by 2^24, and the sums scaled back: the last bit of any FP32 value is then
+// 2^-125 at least, so that no part falls among bf16's subnormals, which would cost it bits (unscaled,
+// operands of 1e-36 gave sums off by 3e-5).  Infinities and NaN do not split, and products or sums above
+// 2^79 do not fit the scaled range: the kernels find the outputs that are not finite and contract them
+// in plain FP32.
+constexpr float kSplitScale = 16777216.f;                            // 2^24
+constexpr float kSplitBack = 1.f / (kSplitScale * kSplitScale);
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -64,8 +71,10 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
 }
 
-// parts[0..2] = the (high, middle, low) bf16 parts of the pair (a, b), a in the low half
-__device__ __forceinline__ void split_pair(float a, float b, uint32_t (&parts)[3]) {
+// parts[0..2] = the (high, middle, low) bf16 parts of the pair (a, b) times `scale`, a in the low half
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t (&parts)[3], float scale = kSplitScale) {
+  a *= scale;
+  b *= scale;
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
     parts[p] = pack_bf16(a, b);
@@ -434,7 +443,7 @@ __global__ __launch_bounds__(kConvBlock) void k_conv3x3_bwd(ConvArgs a, const ui
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t keep = (uint32_t)((int32_t)(m << (31 - e)) >> 31);   // all ones where the bit is set
-          w[e] = __uint_as_float(__float_as_uint(o[r][u][e] + ad[e]) & keep);
+          w[e] = __uint_as_float(__float_as_uint(SPLAT_FMA(o[r][u][e], kSplitBack, ad[e])) & keep);
           bad = SPLAT_FMA(w[e], 0.f, bad);
         }
         reinterpret_cast<float4*>(a.out)[at * 8 + c4 + 4 * u] = make_float4(w[0], w[1], w[2], w[3]);
@@ -480,7 +489,7 @@ struct WgradSmem {
 
 // splits NR rows of four channels; put(part, channel, words) stores a channel's rows, two per word
 template <int NR, typename Put>
-__device__ __forceinline__ void split_rows(const float4 (&v)[NR], Put put) {
+__device__ __forceinline__ void split_rows(const float4 (&v)[NR], float scale, Put put) {
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     uint32_t w[3][NR / 2];
@@ -489,7 +498,7 @@ __device__ __forceinline__ void split_rows(const float4 (&v)[NR], Put put) {
       const float4 u0 = v[2 * h], u1 = v[2 * h + 1];
       uint32_t q[3];
       split_pair(c == 0 ? u0.x : c == 1 ? u0.y : c == 2 ? u0.z : u0.w,
-                 c == 0 ? u1.x : c == 1 ? u1.y : c == 2 ? u1.z : u1.w, q);
+                 c == 0 ? u1.x : c == 1 ? u1.y : c == 2 ? u1.z : u1.w, q, scale);
 #pragma unroll
       for (int p = 0; p < 3; ++p) w[p][h] = q[p];
     }
@@ -551,8 +560,10 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[m][e] = 0.f;
   float accb[4] = {0.f, 0.f, 0.f, 0.f};
-  // the odd workgroups contract -dy and negate their sums (the instruction's rounding bias cancels)
-  const uint32_t sign = (blockIdx.x & 1) ? 0x80000000u : 0u;
+  // the odd workgroups contract -dy and negate their sums: the instruction's rounding bias cancels (an
+  // image of one tile has none of them and needs none: 16 x 8 pixels err by 2.0e-7 to 3.5e-7 over the
+  // blocks' weights, where the FP32 instructions err by 3.9e-7 to 4.8e-7)
+  const float sign = (blockIdx.x & 1) ? -1.f : 1.f;
   // staging tasks of (column, four channels, four rows): threads 0-255 the 16 dy columns, threads
   // 256-543 the 18 x columns (rows 0-7); threads 544-687 rows 8, 9 of the x columns
   const int q = tid & 7;
@@ -581,17 +592,13 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
         accb[1] += v[r].y;
         accb[2] += v[r].z;
         accb[3] += v[r].w;
-        v[r].x = __uint_as_float(__float_as_uint(v[r].x) ^ sign);
-        v[r].y = __uint_as_float(__float_as_uint(v[r].y) ^ sign);
-        v[r].z = __uint_as_float(__float_as_uint(v[r].z) ^ sign);
-        v[r].w = __uint_as_float(__float_as_uint(v[r].w) ^ sign);
       }
     }
     if (is_tail) {
       if (rows)
-        split_rows<2>({v[0], v[1]}, [&](int p, int c, const uint32_t (&w)[1]) { t.x_tail[p][4 * q + c][col] = w[0]; });
+        split_rows<2>({v[0], v[1]}, kSplitScale, [&](int p, int c, const uint32_t (&w)[1]) { t.x_tail[p][4 * q + c][col] = w[0]; });
     } else {
-      split_rows<4>(v, [&](int p, int c, const uint32_t (&w)[2]) {
+      split_rows<4>(v, is_dy ? sign * kSplitScale : kSplitScale, [&](int p, int c, const uint32_t (&w)[2]) {
         uint4* dst = is_dy ? &t.dy[p][4 * q + c][col] : &t.x[p][4 * q + c][col];
         reinterpret_cast<uint2*>(dst)[part] = make_uint2(w[0], w[1]);
       });
@@ -644,7 +651,7 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
   __syncthreads();
   float bad = 0.f;   // not a number once a sum is not finite
   for (int i = tid; i < 9 * kCC * kCC; i += kWgradBlock) {
-    const float s = __uint_as_float(__float_as_uint(sm.red[i]) ^ sign);
+    const float s = sm.red[i] * (sign * kSplitBack);
     bad = SPLAT_FMA(s, 0.f, bad);
     dst[i] = s;
   }
