@@ -96,19 +96,31 @@ __device__ constexpr int prod_acc(int i) { return i == 0 ? 0 : i == 1 ? 1 : i ==
 
 // 16-byte image loads through a buffer descriptor: an offset past its size reads zeros, so pixels
 // outside the image cost a select instead of a branch around each load.  The window starts at pixel
-// row y0 of a 32-channel image (rows before the image are only ever given the outside offset).
+// row y0 of a 32-channel image (rows before the image are only ever given the outside offset), and its
+// bytes stay below 2^31 up to kMaxWidth.  WIDE: for wider images, plain 64-bit addresses, the first
+// pixel's where there is none (1000000 x 16, forward and adjoint: 38 ms; with an output per lane on the
+// vector units instead of these kernels 3.7 s).
+constexpr int kMaxWidth = 900000;
+
+template <bool WIDE>
 struct Window {
+  const float4* img;
+  int W, y0;
   __amdgpu_buffer_rsrc_t rsrc;
-  __device__ __forceinline__ Window(const float* img, int W, int y0, int rows) {
-    rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(img + (int64_t)y0 * W * 32), 0, rows * W * 128, 0x00027000);
+  __device__ __forceinline__ Window(const float* img, int W, int y0, int rows)
+      : img(reinterpret_cast<const float4*>(img)), W(W), y0(y0) {
+    if (!WIDE)
+      rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(img + (int64_t)y0 * W * 32), 0, rows * W * 128, 0x00027000);
   }
-  __device__ __forceinline__ float4 load(bool inside, int offset) const {
+  // piece q (16 bytes) of pixel (x, y0 + row), at `offset` from the window's start
+  __device__ __forceinline__ float4 load(bool inside, int offset, int row, int x, int q) const {
+    if (WIDE) {
+      const float4 v = img[inside ? ((int64_t)(y0 + row) * W + x) * 8 + q : 0];
+      return inside ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, inside ? offset : -1, 0, 0));
   }
 };
-
-// a window's bytes stay below 2^31 up to this width; wider images take k_conv_plain
-constexpr int kMaxWidth = 900000;
 
 struct ConvArgs {
   const float* in;      // [H*W][32]
@@ -192,6 +204,7 @@ constexpr int kHaloVec = kHalo * kHalo * 8;                                  // 
 constexpr int kHaloPer = (kHaloVec + kConvBlock - 1) / kConvBlock;           // per thread
 
 // A thread's pieces of a halo: their place in the window and in memory, the same for every tile.
+template <bool WIDE>
 struct HaloLoad {
   int off[kHaloPer], row[kHaloPer], col[kHaloPer];
   __device__ __forceinline__ explicit HaloLoad(int W) {
@@ -200,26 +213,27 @@ struct HaloLoad {
       const int i = threadIdx.x + kConvBlock * j, pix = i >> 3;
       row[j] = i < kHaloVec ? pix / kHalo : (1 << 30);   // past every image
       col[j] = pix % kHalo;
-      off[j] = (pix / kHalo * W + col[j]) * 128 + 16 * (i & 7);
+      off[j] = WIDE ? 0 : (pix / kHalo * W + col[j]) * 128 + 16 * (i & 7);
     }
   }
   __device__ __forceinline__ void load(float4 (&v)[kHaloPer], const ConvArgs& a, int tile, int tiles_x) const {
     const int ty0 = tile / tiles_x * kTS - 1, tx0 = tile % tiles_x * kTS - 1;
-    const Window win(a.in, a.W, ty0, kHalo);
+    const Window<WIDE> win(a.in, a.W, ty0, kHalo);
 #pragma unroll
     for (int j = 0; j < kHaloPer; ++j)
       v[j] = win.load((unsigned)(ty0 + row[j]) < (unsigned)a.H && (unsigned)(tx0 + col[j]) < (unsigned)a.W,
-                      off[j] + tx0 * 128);
+                      WIDE ? 0 : off[j] + tx0 * 128, row[j], tx0 + col[j], threadIdx.x & 7);
   }
 };
 
+template <bool WIDE>
 __global__ __launch_bounds__(kConvBlock) void k_conv3x3(ConvArgs a, const float4* __restrict__ frag) {
   __shared__ float4 s_in[2][kHalo * kHalo * kLS / 4];
   __shared__ float4 s_w[kFrag / 4];
   const int tiles_x = (a.W + kTS - 1) / kTS, n_tiles = tiles_x * ((a.H + kTS - 1) / kTS);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int li = lane & 15, lk = lane >> 4;
-  const HaloLoad halo(a.W);
+  const HaloLoad<WIDE> halo(a.W);
   float4 v[kHaloPer];
   auto load = [&](int tile) { halo.load(v, a, tile < n_tiles ? tile : n_tiles - 1, tiles_x); };
   auto stage = [&](float4* dst) {
@@ -321,24 +335,6 @@ __device__ __forceinline__ float conv_plain(const ConvArgs& a, int y, int x, int
   return s;
 }
 
-// Either convolution for images wider than kMaxWidth: a thread per output, 32 channels of a pixel in
-// consecutive lanes.
-__global__ __launch_bounds__(256) void k_conv_plain(ConvArgs a) {
-  const int64_t n = (int64_t)a.W * a.H * kCC;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {   // n % 32 == 0
-    const int64_t at = i / kCC;
-    const int c = (int)(i % kCC);
-    float v = conv_plain(a, (int)(at / a.W), (int)(at % a.W), c);
-    if (!a.transpose) v += a.bias[c];
-    if (a.addend) v += a.addend[i];
-    if (!a.transpose) v = fmaxf(v, 0.f);
-    if (a.mask) v = (a.mask[at] >> c) & 1u ? v : 0.f;
-    a.out[i] = v;
-    const uint64_t on = __ballot(v > 0.f);
-    if (a.bits_out && c == 0) a.bits_out[at] = (uint32_t)(on >> (threadIdx.x & 32));
-  }
-}
-
 // Input-gradient convolution on the bf16 matrix cores (split operands, see above).  Persistent
 // workgroups of eight wavefronts, one workgroup per compute unit, compute 16 x 16-pixel tiles; a
 // wavefront owns 2 pixel rows, and an MFMA contracts 16 channels for 32 output channels (operand A,
@@ -351,6 +347,7 @@ __global__ __launch_bounds__(256) void k_conv_plain(ConvArgs a) {
 // per compute unit do not keep HBM busy).
 constexpr int kSplitRow = 13;     // uint4 per pixel in LDS: 3 parts x 4, and one of padding
 
+template <bool WIDE>
 __global__ __launch_bounds__(kConvBlock) void k_conv3x3_bwd(ConvArgs a, const uint4* __restrict__ frag) {
   __shared__ uint4 s_in[kHalo * kHalo * kSplitRow];
   __shared__ uint4 s_w[kSplitFrag];
@@ -361,7 +358,7 @@ __global__ __launch_bounds__(kConvBlock) void k_conv3x3_bwd(ConvArgs a, const ui
   // pieces c4 and c4 + 4: 64 contiguous bytes per 4 lanes (16-byte pieces of other lines would cost
   // twice the bytes written to HBM)
   const int c4 = 2 * pr + kh;
-  const HaloLoad halo(a.W);
+  const HaloLoad<WIDE> halo(a.W);
   float4 va[kHaloPer], vb[kHaloPer];   // the next two tiles' halos
   // unconditional: no branch around the loads
   auto load = [&](float4 (&v)[kHaloPer], int tile) { halo.load(v, a, tile < n_tiles ? tile : n_tiles - 1, tiles_x); };
@@ -508,7 +505,7 @@ __device__ __forceinline__ void split_rows(const float4 (&v)[NR], float scale, P
 }
 
 // The workgroup's partial sums that are not finite, once more in plain FP32 (values that do not split
-// end up there: a part of theirs is not a number).  Images wider than kMaxWidth take it for all.
+// end up there: a part of theirs is not a number).
 __device__ __forceinline__ void wgrad_plain(const float* __restrict__ x, const float* __restrict__ dy, int H, int W,
                                             float* __restrict__ dst) {
   const int tiles_x = (W + kTS - 1) / kTS, tiles_y = (H + kWTH - 1) / kWTH;
@@ -527,6 +524,7 @@ __device__ __forceinline__ void wgrad_plain(const float* __restrict__ x, const f
   }
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(kWgradBlock)
 void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, int H, int W, float* __restrict__ partial) {
   __shared__ union {
@@ -540,20 +538,6 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
   const int ch = lane & 31, kh = lane >> 5;
   const int kx = wave % 3, quarter = wave / 3;
   float* dst = partial + (int64_t)blockIdx.x * kWOut;
-  if (W > kMaxWidth) {   // uniform
-    for (int i = tid; i < 9 * kCC * kCC; i += kWgradBlock) dst[i] = INFINITY;
-    wgrad_plain(x, dy, H, W, dst);
-    if (tid < kCC) {
-      float s = 0.f;
-      for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)
-        for (int p = 0; p < kWTH * kTS; ++p) {
-          const int yy = tile / tiles_x * kWTH + p / kTS, xx = tile % tiles_x * kTS + p % kTS;
-          if (yy < H && xx < W) s += dy[((int64_t)yy * W + xx) * kCC + tid];
-        }
-      dst[9 * kCC * kCC + tid] = s;
-    }
-    return;
-  }
   floatx16 acc[3];
 #pragma unroll
   for (int m = 0; m < 3; ++m)
@@ -572,17 +556,19 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
   const int part = tid < 544 ? (tid >> 3) & 1 : 2;   // rows 4 part ...
   const int col = is_dy ? tid >> 4 : is_tail ? (tid - 544) >> 3 : (tid - 256) >> 4;
   const int r0 = 4 * part + (is_dy ? 1 : 0);   // from the row above the tile
-  const int off = (r0 * W + (is_dy ? col : col - 1)) * 128 + 16 * q;
+  const int off = WIDE ? 0 : (r0 * W + (is_dy ? col : col - 1)) * 128 + 16 * q;
   const int rows = tid < 544 ? 4 : tid < 688 ? 2 : 0;
   float4 v[4];
   auto load = [&](int tile) {   // in flight while the previous tile is contracted
     tile = tile < n_tiles ? tile : n_tiles - 1;   // unconditional: no branch around the loads
     const int ty0 = tile / tiles_x * kWTH - 1, tx0 = tile % tiles_x * kTS;
-    const bool in_x = (unsigned)(tx0 + (is_dy ? col : col - 1)) < (unsigned)W;
-    const Window win(is_dy_wave ? dy : x, W, ty0, kWTH + 2);
+    const int px = tx0 + (is_dy ? col : col - 1);
+    const bool in_x = (unsigned)px < (unsigned)W;
+    const Window<WIDE> win(is_dy_wave ? dy : x, W, ty0, kWTH + 2);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      v[r] = win.load(in_x && r < rows && (unsigned)(ty0 + r0 + r) < (unsigned)H, off + (r * W + tx0) * 128);
+      v[r] = win.load(in_x && r < rows && (unsigned)(ty0 + r0 + r) < (unsigned)H, WIDE ? 0 : off + (r * W + tx0) * 128,
+                      r0 + r, px, q);
   };
   auto stage = [&](WgradSmem& t) {   // splits the loaded values into a buffer
     if (is_dy) {   // uniform over the wavefront
@@ -1018,11 +1004,8 @@ static ConvWeights conv_weights(const SplatCameraCNN* cnn, int cin) {
 static hipError_t conv(int k, const float* in, float* out, const ConvWeights& cw, const float* bias, const float* addend,
                        int W, int H, const CnnWs& w, hipStream_t s) {
   ConvArgs a{in, out, cw.w[k], cw.ci_n[k], kCC, 0, bias, addend, k < 4 ? w.bits[k] : nullptr, nullptr, H, W};
-  if (W > kMaxWidth)
-    hipLaunchKernelGGL(k_conv_plain, dim3(4096), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_conv3x3, dim3(conv_grid(W, H)), dim3(kConvBlock), 0, s, a,
-                       (const float4*)(w.frag + (size_t)k * kFrag));
+  hipLaunchKernelGGL(W > kMaxWidth ? k_conv3x3<true> : k_conv3x3<false>, dim3(conv_grid(W, H)), dim3(kConvBlock), 0, s,
+                     a, (const float4*)(w.frag + (size_t)k * kFrag));
   return hipGetLastError();
 }
 
@@ -1030,18 +1013,16 @@ static hipError_t conv(int k, const float* in, float* out, const ConvWeights& cw
 static hipError_t conv_bwd(int k, const float* in, float* out, const ConvWeights& cw, const float* addend,
                            const uint32_t* mask, int W, int H, const CnnWs& w, hipStream_t s) {
   ConvArgs a{in, out, cw.w[k], cw.ci_n[k], kCC, 1, nullptr, addend, nullptr, mask, H, W};
-  if (W > kMaxWidth)
-    hipLaunchKernelGGL(k_conv_plain, dim3(4096), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_conv3x3_bwd, dim3(conv_grid(W, H)), dim3(kConvBlock), 0, s, a,
-                       (const uint4*)(w.sfrag + (size_t)k * kSplitFrag));
+  hipLaunchKernelGGL(W > kMaxWidth ? k_conv3x3_bwd<true> : k_conv3x3_bwd<false>, dim3(conv_grid(W, H)),
+                     dim3(kConvBlock), 0, s, a, (const uint4*)(w.sfrag + (size_t)k * kSplitFrag));
   return hipGetLastError();
 }
 
 static hipError_t wgrad(const float* x, const float* dy, int ci_n, int co_n, float* dw, float* db, float* partial, int W,
                         int H, hipStream_t s) {
   const int nb = wgrad_blocks(W, H);
-  hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((unsigned)nb), dim3(kWgradBlock), 0, s, x, dy, H, W, partial);
+  hipLaunchKernelGGL(W > kMaxWidth ? k_conv3x3_wgrad<true> : k_conv3x3_wgrad<false>, dim3((unsigned)nb),
+                     dim3(kWgradBlock), 0, s, x, dy, H, W, partial);
   launch_column_sums((const float*)partial, kWOut, nb, kWOut, ConvGradStore{dw, db, ci_n, co_n}, s);
   return hipGetLastError();
 }
