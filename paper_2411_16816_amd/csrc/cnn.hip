@@ -60,7 +60,7 @@ __device__ __forceinline__ floatx4 mfma4(float a, float b, floatx4 c) {
 // 2^-125 at least, so that no part falls among bf16's subnormals, which would cost it bits (unscaled,
 // operands of 1e-36 gave sums off by 3e-5).  Infinities and NaN do not split, and products or sums above
 // 2^79 do not fit the scaled range: the kernels find the outputs that are not finite and contract them
-// in plain FP32.
+// with the FP32 instructions.
 constexpr float kSplitScale = 16777216.f;                            // 2^24
 constexpr float kSplitBack = 1.f / (kSplitScale * kSplitScale);
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -323,18 +323,6 @@ __global__ __launch_bounds__(kConvBlock) void k_conv3x3(ConvArgs a, const float4
   }
 }
 
-// One output of a convolution in plain FP32 from global memory.
-__device__ __forceinline__ float conv_plain(const ConvArgs& a, int y, int x, int co) {
-  float s = 0.f;
-  for (int tap = 0; tap < 9; ++tap) {
-    const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
-    if (yy < 0 || yy >= a.H || xx < 0 || xx >= a.W) continue;
-    for (int c = 0; c < kCC; ++c)
-      s = fmaf(a.in[((int64_t)yy * a.W + xx) * kCC + c], conv_w(a, c, co, tap / 3, tap % 3), s);
-  }
-  return s;
-}
-
 // Input-gradient convolution on the bf16 matrix cores (split operands, see above).  Persistent
 // workgroups of eight wavefronts, one workgroup per compute unit, compute 16 x 16-pixel tiles; a
 // wavefront owns 2 pixel rows, and an MFMA contracts 16 channels for 32 output channels (operand A,
@@ -346,6 +334,75 @@ __device__ __forceinline__ float conv_plain(const ConvArgs& a, int y, int x, int
 // all banks).  The next two tiles' loads are in flight while this one is contracted (one tile's 41 KB
 // per compute unit do not keep HBM busy).
 constexpr int kSplitRow = 13;     // uint4 per pixel in LDS: 3 parts x 4, and one of padding
+
+// The outputs of the wavefront's tiles that are not finite, once more with the FP32 instructions, from
+// global memory (operands as in k_conv3x3).  Masked outputs are zero and stay.  With an output at a time
+// on the vector units an upstream gradient without a finite value made 640 x 360 pixels take 39.6 ms
+// forward and adjoint, this way and with wgrad_fp32 2.4; with one such value 16.1, now 1.5; with none 0.73.
+__device__ __forceinline__ void conv_bwd_fp32(const ConvArgs& a, int n_tiles, int tiles_x) {
+  const int wave = threadIdx.x >> 6, li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
+  __threadfence_block();   // the stores of the wavefront's other lanes
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    const int x = tile % tiles_x * kTS + li, y0 = tile / tiles_x * kTS + wave * 2;
+    float o[2][2][4];   // as stored: [pixel row][channel half]; zero outside the image
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool ok = y0 + r < a.H && x < a.W;
+        const int64_t at = ok ? (int64_t)(y0 + r) * a.W + x : 0;
+        const float4 v = reinterpret_cast<const float4*>(a.out)[at * 8 + 4 * h + lk];
+        o[r][h][0] = ok ? v.x : 0.f;
+        o[r][h][1] = ok ? v.y : 0.f;
+        o[r][h][2] = ok ? v.z : 0.f;
+        o[r][h][3] = ok ? v.w : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad = bad || !finite_f(o[r][h][e]);
+      }
+    if (!__any(bad)) continue;
+    floatx4 acc[2][2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc[r][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int tap = 0; tap < 9; ++tap) {
+      float xf[2][8];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int yy = y0 + r + tap / 3 - 1, xx = x + tap % 3 - 1;
+        const bool ok = (unsigned)yy < (unsigned)a.H && (unsigned)xx < (unsigned)a.W;
+        const float4* in = reinterpret_cast<const float4*>(a.in) + (ok ? (int64_t)yy * a.W + xx : 0) * 8 + 2 * lk;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float4 v = in[q];
+          xf[r][4 * q] = ok ? v.x : 0.f;
+          xf[r][4 * q + 1] = ok ? v.y : 0.f;
+          xf[r][4 * q + 2] = ok ? v.z : 0.f;
+          xf[r][4 * q + 3] = ok ? v.w : 0.f;
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float wf = conv_w(a, 8 * lk + s, 16 * h + li, tap / 3, tap % 3);
+#pragma unroll
+          for (int r = 0; r < 2; ++r) acc[r][h] = mfma4(wf, xf[r][s], acc[r][h]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (finite_f(o[r][h][e])) continue;
+          const int64_t i = ((int64_t)(y0 + r) * a.W + x) * kCC + 16 * h + 4 * lk + e;
+          a.out[i] = a.addend ? acc[r][h][e] + a.addend[i] : acc[r][h][e];
+        }
+  }
+}
 
 template <bool WIDE>
 __global__ __launch_bounds__(kConvBlock) void k_conv3x3_bwd(ConvArgs a, const uint4* __restrict__ frag) {
@@ -451,17 +508,7 @@ __global__ __launch_bounds__(kConvBlock) void k_conv3x3_bwd(ConvArgs a, const ui
     tile_step(va, tile);
     if (tile + (int)gridDim.x < n_tiles) tile_step(vb, tile + gridDim.x);   // uniform
   }
-  if (bad == 0.f) return;   // else the lane's own stores that are not finite, in plain FP32
-  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x)
-    for (int i = 0; i < 16; ++i) {
-      const int y = tile / tiles_x * kTS + wave * 2 + (i >> 3), x = tile % tiles_x * kTS + px;
-      const int c = 4 * c4 + 16 * ((i >> 2) & 1) + (i & 3);
-      if (y >= a.H || x >= a.W) continue;
-      const int64_t at = (int64_t)y * a.W + x;
-      if (finite_f(a.out[at * kCC + c])) continue;   // masked outputs are zero
-      const float s = conv_plain(a, y, x, c);
-      a.out[at * kCC + c] = a.addend ? s + a.addend[at * kCC + c] : s;
-    }
+  if (__any(bad != 0.f)) conv_bwd_fp32(a, n_tiles, tiles_x);
 }
 
 // Weight gradient dW[tap][ci][co] = sum_p x[p + tap][ci] dy[p][co] on the bf16 matrix cores (split
@@ -504,23 +551,36 @@ __device__ __forceinline__ void split_rows(const float4 (&v)[NR], float scale, P
   }
 }
 
-// The workgroup's partial sums that are not finite, once more in plain FP32 (values that do not split
-// end up there: a part of theirs is not a number).
-__device__ __forceinline__ void wgrad_plain(const float* __restrict__ x, const float* __restrict__ dy, int H, int W,
-                                            float* __restrict__ dst) {
+// The workgroup's partial sums that are not finite, once more with the FP32 instructions, from global
+// memory: a block of 16 input x 16 output channels of a tap is contracted over four pixels at a time, three
+// blocks to a wavefront.  A tap's pixels outside the image add nothing, whatever the other operand.
+__device__ __forceinline__ void wgrad_fp32(const float* __restrict__ x, const float* __restrict__ dy, int H, int W,
+                                           float* __restrict__ dst) {
   const int tiles_x = (W + kTS - 1) / kTS, tiles_y = (H + kWTH - 1) / kWTH;
-  for (int i = threadIdx.x; i < 9 * kCC * kCC; i += kWgradBlock) {
-    if (finite_f(dst[i])) continue;
-    const int tap = i / (kCC * kCC), ci = (i / kCC) % kCC, co = i % kCC;
-    float s = 0.f;
+  const int li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
+  constexpr int kBlocks = 36 / (kWgradBlock / 64);
+  for (int b = 0; b < kBlocks; ++b) {
+    const int blk = (int)(threadIdx.x >> 6) * kBlocks + b, tap = blk >> 2;
+    const int ci0 = 16 * ((blk >> 1) & 1), co0 = 16 * (blk & 1);
+    floatx4 acc{0.f, 0.f, 0.f, 0.f};
     for (int tile = blockIdx.x; tile < tiles_x * tiles_y; tile += gridDim.x)
-      for (int p = 0; p < kWTH * kTS; ++p) {
-        const int yy = tile / tiles_x * kWTH + p / kTS, xx = tile % tiles_x * kTS + p % kTS;
-        const int ys = yy + tap / 3 - 1, xs = xx + tap % 3 - 1;
-        if (yy >= H || xx >= W || ys < 0 || ys >= H || xs < 0 || xs >= W) continue;
-        s = fmaf(x[((int64_t)ys * W + xs) * kCC + ci], dy[((int64_t)yy * W + xx) * kCC + co], s);
+      for (int y = 0; y < kWTH; ++y) {
+        const int yy = tile / tiles_x * kWTH + y, ys = yy + tap / 3 - 1;
+        if (yy >= H || ys < 0 || ys >= H) continue;   // uniform
+#pragma unroll
+        for (int c = 0; c < kTS; c += 4) {
+          const int xx = tile % tiles_x * kTS + c + lk, xs = xx + tap % 3 - 1;
+          const bool ok = xx < W && xs >= 0 && xs < W;
+          const float xv = x[((int64_t)ys * W + (ok ? xs : 0)) * kCC + ci0 + li];
+          const float dv = dy[((int64_t)yy * W + (ok ? xx : 0)) * kCC + co0 + li];
+          acc = mfma4(ok ? xv : 0.f, ok ? dv : 0.f, acc);
+        }
       }
-    dst[i] = s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = (tap * kCC + ci0 + 4 * lk + e) * kCC + co0 + li;
+      if (!finite_f(dst[i])) dst[i] = acc[e];
+    }
   }
 }
 
@@ -652,7 +712,7 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
     for (int c = 0; c < 16; ++c) s += sm.b[c * 8 + (tid >> 2)][0][tid & 3] + sm.b[c * 8 + (tid >> 2)][1][tid & 3];
     dst[9 * kCC * kCC + tid] = s;
   }
-  if (bad != 0.f) wgrad_plain(x, dy, H, W, dst);   // its loop visits the same entries per thread
+  if (__syncthreads_or(bad != 0.f)) wgrad_fp32(x, dy, H, W, dst);   // all of dst is stored
 }
 
 // dW (OIHW, +=) and db (+=) of one convolution from the column sums of the partials

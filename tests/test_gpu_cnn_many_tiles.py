@@ -26,3 +26,25 @@ def test_many_tiles(w, h):
     _check(I, dF, g, ref, r, image=False)
     bad = np.abs(I - ref) > 1e-4 * np.abs(ref) + 1e-5 * np.abs(ref).max()
     assert not bad.any(), (int(bad.sum()), float(np.abs(I - ref).max()), float(np.abs(ref).max()))
+
+
+def test_large_values_in_later_tiles():
+    """Two upstream values of 3e30, whose products do not fit the scaled bf16 parts' range, in the third and
+    the fourth tile of their workgroups: those outputs and weight sums are contracted again, and nothing
+    outside the network's reach changes."""
+    b = _binding()
+    w, h = 480, 480
+    rng = np.random.default_rng(15)
+    print("[cnn many tiles] large values", flush=True)
+    cam = _camera(w, h)
+    W = _active(_weights(rng, 16, 8))
+    F = _f32(rng.normal(size=(h, w, 16)))
+    dI = _f32(rng.normal(size=(h, w, 3)))
+    clean = _run(b, cam, W, F, dI)
+    far = np.ones((h, w), bool)
+    for y, x in ((300, 33), (470, 477)):   # convolution tiles 542 and 899 of 900
+        dI[y, x, 1] = 3.0e30
+        far[y - 5:y + 6, x - 5:x + 6] = False
+    I, dF, g = _run(b, cam, W, F, dI)
+    assert np.array_equal(I, clean[0]) and np.array_equal(dF[far], clean[1][far])
+    _check(I, dF, g, *_oracle(F, cam, W, dI), image=False)
