@@ -209,6 +209,37 @@ struct DecRows {
   float dpre[kDecHidden][kDecChunk + 4];
 };
 
+// A workgroup's sums of W1, b1 (blocks of the contraction over its rays) and b2 (per lane) to its row of
+// partial sums.
+template <int CM>
+__device__ __forceinline__ void dec_store_sums(float* __restrict__ dst, int C, int lane,
+                                               const decx4 (&acc)[2 * dec_xtiles<CM>()], float gb0, float gb1) {
+  constexpr int NXT = dec_xtiles<CM>(), NT = 2 * NXT;
+  const int XC = C + 3, nw1 = kDecHidden * XC, nw2 = nw1 + 3 * kDecHidden, li = lane & 15, lk = lane >> 4;
+  // D[i][j] of a block: lane j + 16 (i / 4), element i % 4
+#pragma unroll
+  for (int b = 0; b < NT; ++b) {
+    const int jh = b / NXT, nt = b % NXT;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = 16 * jh + 4 * lk + e, col = 16 * nt + li;
+      const float v = acc[b][e];
+      if (col < C) dst[j * XC + col] = v;                                     // feature columns of W1
+      else if (col >= CM && col < CM + 3) dst[j * XC + C + (col - CM)] = v;   // direction columns
+      else if (col == CM + 3) dst[nw1 + j] = v;                               // b1
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    gb0 += __shfl_xor(gb0, o, 64);
+    gb1 += __shfl_xor(gb1, o, 64);
+  }
+  if (lane == 0) {
+    dst[nw2] = gb0;
+    dst[nw2 + 1] = gb1;
+  }
+}
+
 template <int CM, bool VEC>
 __global__ __launch_bounds__(kDecChunk) __attribute__((amdgpu_waves_per_eu(2)))
 void k_lidar_decode_bwd(int64_t n, const float* __restrict__ feat, const float* __restrict__ az,
@@ -220,7 +251,7 @@ void k_lidar_decode_bwd(int64_t n, const float* __restrict__ feat, const float* 
   constexpr int NF = (CM + 15) / 16;     // tiles of 16 features of dL/dF
   __shared__ DecRows<CM> S;
   const int C = VEC ? CM : m.n_feat, XC = C + 3;
-  const int nw1 = kDecHidden * XC, nb1 = nw1 + kDecHidden, nw2 = nb1 + 2 * kDecHidden;
+  const int nb1 = kDecHidden * XC + kDecHidden;
   const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4, half = lane >> 5;
   const DecFirst<CM> first(m, C, lane);
   const DecOutput w(m, half);
@@ -331,35 +362,13 @@ void k_lidar_decode_bwd(int64_t n, const float* __restrict__ feat, const float* 
     }
   }
   float* dst = partial + (int64_t)blockIdx.x * n_out;
-  // D[i][j] of a block: lane j + 16 (i / 4), element i % 4
-#pragma unroll
-  for (int b = 0; b < NT; ++b) {
-    const int jh = b / NXT, nt = b % NXT;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int j = 16 * jh + 4 * lk + e, col = 16 * nt + li;
-      const float v = acc[b][e];
-      if (col < C) dst[j * XC + col] = v;                                     // feature columns of W1
-      else if (col >= CM && col < CM + 3) dst[j * XC + C + (col - CM)] = v;   // direction columns
-      else if (col == CM + 3) dst[nw1 + j] = v;                               // b1
-    }
-  }
-  // W2: the sums over the 32 lanes of each half (the two halves hold different hidden units); b2: two
-  // wavefront sums
+  dec_store_sums<CM>(dst, C, lane, acc, gb0, gb1);
+  // W2: the sums over the 32 lanes of each half (the two halves hold different hidden units)
 #pragma unroll
   for (int i = 0; i < 32; ++i) {
 #pragma unroll
     for (int o = 16; o >= 1; o >>= 1) gw2[i] += __shfl_xor(gw2[i], o, 64);
     if ((lane & 31) == 0) dst[nb1 + kDecHidden * (i >> 4) + dec_hidden(i & 15, half)] = gw2[i];
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    gb0 += __shfl_xor(gb0, o, 64);
-    gb1 += __shfl_xor(gb1, o, 64);
-  }
-  if (lane == 0) {
-    dst[nw2] = gb0;
-    dst[nw2 + 1] = gb1;
   }
 }
 
@@ -367,12 +376,12 @@ void k_lidar_decode_bwd(int64_t n, const float* __restrict__ feat, const float* 
 // With 8 channels in 16-byte rows the first layer is short enough that one lane per ray, with the
 // weights in scalar registers (every lane uses the same weight: scalar loads through the constant
 // address space, a row's loads merged), needs no more instructions than the matrix form spends around
-// its products, at 3 wavefronts per SIMD instead of 2: 16.8M rays 0.82 ms against 0.84.
+// its products, at 3 wavefronts per SIMD instead of 2: 16.8M rays 0.82 to 0.83 ms against 0.84 to 0.85 (262144
+// rays, two latency chains: 33.4 us against 32.9).
 typedef const __attribute__((address_space(4))) float* ConstF;
 
-template <int CM>
-__device__ __forceinline__ float hidden_pre_s(ConstF w1, ConstF b1, int j, const float (&F)[CM],
-                                              const float (&d)[3]) {
+__device__ __forceinline__ float hidden_pre_s(ConstF w1, ConstF b1, int j, const float (&F)[8], const float (&d)[3]) {
+  constexpr int CM = 8;
   const int row = j * (CM + 3);
   float p = b1[j];
 #pragma unroll
@@ -383,26 +392,24 @@ __device__ __forceinline__ float hidden_pre_s(ConstF w1, ConstF b1, int j, const
 }
 
 // One chunk's rows for the first-layer contraction (+1 column: conflict-free row writes)
-template <int CM>
 struct DecLaneRows {
-  float x[kDecChunk][16 * dec_xtiles<CM>() + 1];   // [F, d, 1, 0...]
+  float x[kDecChunk][16 * dec_xtiles<8>() + 1];     // [F, d, 1, 0...]
   float dpre[kDecChunk][kDecHidden + 1];            // pre-activation, then its gradient
 };
 
 // at least 3 wavefronts per SIMD: the output-layer sums take 66 registers per lane
-template <int CM>
 __global__ __launch_bounds__(kDecChunk) __attribute__((amdgpu_waves_per_eu(3)))
 void k_lidar_decode_bwd_valu(int64_t n, const float* __restrict__ feat, const float* __restrict__ az,
                              const float* __restrict__ el, SplatLidarMLP m, const float* __restrict__ d_int,
-                        const float* __restrict__ d_drop, float* __restrict__ d_feat, float* __restrict__ partial,
-                        int n_out) {
+                             const float* __restrict__ d_drop, float* __restrict__ d_feat,
+                             float* __restrict__ partial, int n_out) {
+  constexpr int CM = 8;
   constexpr int NXT = dec_xtiles<CM>();
   constexpr int NT = 2 * NXT;   // [dW1 | db1] blocks: hidden rows 16 (b / NXT) .., x columns 16 (b % NXT) ..
   constexpr int UNR = 4;        // hidden units per unrolled step
-  __shared__ DecLaneRows<CM> S;
+  __shared__ DecLaneRows S;
   const ConstF w1 = (ConstF)m.w1, b1 = (ConstF)m.b1, w2 = (ConstF)m.w2, b2 = (ConstF)m.b2;
-  constexpr int C = CM, XC = C + 3;
-  const int nw1 = kDecHidden * XC, nb1 = nw1 + kDecHidden, nw2 = nb1 + 2 * kDecHidden;
+  constexpr int C = CM, XC = C + 3, nb1 = kDecHidden * XC + kDecHidden;
   decx4 acc[NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i) acc[i] = decx4{0.f, 0.f, 0.f, 0.f};
@@ -413,7 +420,7 @@ void k_lidar_decode_bwd_valu(int64_t n, const float* __restrict__ feat, const fl
   const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4;
   const int64_t step = (int64_t)gridDim.x * kDecChunk;
   for (int64_t base = (int64_t)blockIdx.x * kDecChunk; base < n; base += step) {
-    __syncthreads();   // weights staged / the previous chunk's rows consumed
+    __syncthreads();   // the previous chunk's rows are consumed
     // Lanes past the end work on the last ray with zero upstream gradients: they add nothing,
     // and every load of the chunk is unconditional (issued together, not one branch at a time).
     const int64_t r = base + lane;
@@ -451,7 +458,7 @@ void k_lidar_decode_bwd_valu(int64_t n, const float* __restrict__ feat, const fl
     float z0 = b2[0], z1 = b2[1];
 #pragma unroll UNR
     for (int j = 0; j < kDecHidden; ++j) {
-      const float p = hidden_pre_s<CM>(w1, b1, j, F, d);
+      const float p = hidden_pre_s(w1, b1, j, F, d);
       S.dpre[lane][j] = p;
       const float h = fmaxf(p, 0.f);
       z0 = fmaf(w2[j], h, z0);
@@ -509,33 +516,12 @@ void k_lidar_decode_bwd_valu(int64_t n, const float* __restrict__ feat, const fl
     }
   }
   float* dst = partial + (int64_t)blockIdx.x * n_out;
-  // D[i][j] of a block: lane j + 16 (i / 4), element i % 4
-#pragma unroll
-  for (int b = 0; b < NT; ++b) {
-    const int jh = b / NXT, nt = b % NXT;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int j = 16 * jh + 4 * lk + e, col = 16 * nt + li;
-      const float v = acc[b][e];
-      if (col < C) dst[j * XC + col] = v;                                     // feature columns of W1
-      else if (col >= CM && col < CM + 3) dst[j * XC + C + (col - CM)] = v;   // direction columns
-      else if (col == CM + 3) dst[nw1 + j] = v;                               // b1
-    }
-  }
-  // W2: one value per lane after the wavefront's reduce-scatter; b2: two wavefront sums
+  dec_store_sums<CM>(dst, C, lane, acc, gb0, gb1);
+  // W2: one value per lane after the wavefront's reduce-scatter
   bool store;
   const int slot = scatter_slot<2 * kDecHidden>(lane, store);
   const float w2sum = wave_reduce_scatter<2 * kDecHidden>(gw2);
   if (store) dst[nb1 + slot] = w2sum;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    gb0 += __shfl_xor(gb0, o, 64);
-    gb1 += __shfl_xor(gb1, o, 64);
-  }
-  if (lane == 0) {
-    dst[nw2] = gb0;
-    dst[nw2 + 1] = gb1;
-  }
 }
 
 // weight gradients (+=) from the column sums of the workgroups' partials
@@ -635,7 +621,7 @@ int splat_lidar_decode_bwd(int64_t n_rays, const float* feat, const float* ray_a
   int nb;
 #define DEC_LAUNCH(...) \
   nb = launch_decode_bwd(__VA_ARGS__, n_rays, feat, ray_az, ray_el, w, di, dd, d_feat, partial, n_out, s)
-  if (vec && C == 8) DEC_LAUNCH(k_lidar_decode_bwd_valu<8>);
+  if (vec && C == 8) DEC_LAUNCH(k_lidar_decode_bwd_valu);
   else if (vec && C == 16) DEC_LAUNCH((k_lidar_decode_bwd<16, true>));
   else if (vec && C == 32) DEC_LAUNCH((k_lidar_decode_bwd<32, true>));
   else if (C <= 8) DEC_LAUNCH((k_lidar_decode_bwd<8, false>));
