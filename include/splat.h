@@ -629,8 +629,7 @@ typedef struct SplatGaussianState {
 } SplatGaussianState;
 
 /* Workspace of splat_mcmc_relocate (the scanned weights, counts, targets, the list of the dead with
- * their draws): about 17 bytes per
- * Gaussian; 0 = invalid. */
+ * their draws): about 17 bytes per Gaussian; 0 = invalid. */
 size_t splat_mcmc_relocate_workspace_bytes(int64_t n);
 /* A Gaussian with opacity <= dead_opacity (0.005 in the strategy), or a non-finite one, is
  * dead; each dead Gaussian becomes a copy of an alive target drawn with probability

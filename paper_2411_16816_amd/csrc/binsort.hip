@@ -11,9 +11,10 @@
 //   3. tiles are grouped into supertiles (camera 8 x 8 tiles, lidar 4 x 4); a scan in depth
 //      order gives every record the place of its (supertile, record) entries, one per supertile
 //      its rectangle meets, and they are written in depth order;
-//   4. a stable radix sort by supertile (whose first digit counts the emission leaves) groups those entries, each supertile's in depth order,
-//      and gives each supertile its range of entries (with at most 256 supertiles the sort is
-//      one pass and its scatter writes the ranges from the digit totals; else a ranges pass);
+//   4. a stable radix sort by supertile (whose first digit counts the emission leaves) groups those
+//      entries, each supertile's in depth order, and gives each supertile its range of entries
+//      (with at most 256 supertiles the sort is one pass and its scatter writes the ranges from
+//      the digit totals; else a ranges pass);
 //   5. each supertile's entries are cut into items of at most 256; per item, the entries
 //      meeting each of the supertile's tiles (64 or 16) are counted (wavefront ballots), one scan of the
 //      counts gives every tile its list range and every item its first position in each list,
@@ -107,7 +108,8 @@ __device__ __forceinline__ int64_t sort_count(const int64_t* n_ptr, int64_t n_ca
 // parts.  Consecutive radix tiles' runs of a digit continue each other in the output, and the XCD's L2 then
 // holds the cache lines that they share until both have written; and what a tile's histogram read, its
 // scatter finds there.  2M records: four passes' scatters 74 -> 63 us, their histograms 31 -> 25, the
-// emission 33 -> 30; seven sensors over 1.5M Gaussians 109 -> 89, 38 -> 34, 55 -> 49; 500k records 36 -> 37.  Past the last part for workgroups without one; the grid is xcd_grid(parts at most).
+// emission 33 -> 30; seven sensors over 1.5M Gaussians 109 -> 89, 38 -> 34, 55 -> 49; 500k records
+// 36 -> 37.  Workgroups without a part get one past the last; the grid is xcd_grid(parts at most).
 constexpr int kXcds = 8;
 inline unsigned xcd_grid(int64_t parts) { return (unsigned)(div_up(parts, kXcds) * kXcds); }
 
@@ -183,7 +185,8 @@ __global__ __launch_bounds__(256) void k_radix_colscan(uint32_t* __restrict__ hi
 template <typename K, typename V>
 __global__ __launch_bounds__(256) void k_radix_scatter(const K* __restrict__ kin, const V* __restrict__ vin,
                                                        K* __restrict__ kout, V* __restrict__ vout,
-                                                       const int64_t* n_ptr, int64_t n_cap, int64_t hist_stride, int shift, int bits,
+                                                       const int64_t* n_ptr, int64_t n_cap, int64_t hist_stride,
+                                                       int shift, int bits,
                                                        const uint32_t* __restrict__ hist,
                                                        const uint32_t* __restrict__ coltotal,
                                                        uint2* __restrict__ range_out, int n_range) {
@@ -307,8 +310,8 @@ static hipError_t radix_sort(K* k[2], V* v[2], int& cur, const int64_t* n_ptr, i
     hipLaunchKernelGGL(k_radix_colscan, dim3(kRadixBins), dim3(256), 0, s, hist, n_ptr, n_cap, nb, coltotal);
     V* vdst = (p == passes - 1 && final_vals) ? final_vals : v[1 - cur];
     hipLaunchKernelGGL((k_radix_scatter<K, V>), dim3(xcd_grid(nb)), dim3(256), 0, s,
-                       (const K*)k[cur], (const V*)v[cur], k[1 - cur], vdst, n_ptr, n_cap, nb, shift, bits, (const uint32_t*)hist, (const uint32_t*)coltotal,
-                       range_out, n_range);
+                       (const K*)k[cur], (const V*)v[cur], k[1 - cur], vdst, n_ptr, n_cap, nb, shift, bits,
+                       (const uint32_t*)hist, (const uint32_t*)coltotal, range_out, n_range);
     cur = 1 - cur;
   }
   return hipGetLastError();
@@ -436,8 +439,8 @@ __device__ __forceinline__ void st_rows_cols(const StGrid& S, const int4 rc, int
 // A rectangle in 32 bits, for tile grids of at most kPackGrid rows and columns.  The sort by depth then
 // carries it in the key's upper half, and the number of supertiles it meets in the bits that the record's
 // number leaves free in the value, so that the emission of the entries in depth order reads no rectangle,
-// a random access per record (2M lidar records: emission 57 us with it, 33 without).  Where that does not fit (emit_entries), the
-// key's upper half is the number of supertiles and the rectangle is fetched.
+// a random access per record (2M lidar records: emission 57 us with it, 33 without).  Where that does not
+// fit (emit_entries), the key's upper half is the number of supertiles and the rectangle is fetched.
 constexpr int kPackGrid = 256;
 
 __device__ __forceinline__ uint32_t pack_rect(const int4 rc) {
@@ -455,7 +458,8 @@ __device__ __forceinline__ uint32_t st_total(const StGrid& S, const int4 rc) {
 // Visitor of the record-order scan of (visible, tile count) pairs.  A visible record gets its
 // entry base (the record-order prefix of the tile counts: record r owns the adjoint slots
 // [entry_base, entry_base + n_tiles)) and, at its compacted position, its depth key and its number, with
-// the number of supertiles it meets and the packed rectangle above them (see pack_rect).  The closing block stores the visible and entry counts and the status.
+// the number of supertiles it meets and the packed rectangle above them (see pack_rect).  The closing
+// block stores the visible and entry counts and the status.
 template <bool PACKED>
 struct VisibleVisit {
   const DevSensor* sens;
@@ -565,18 +569,20 @@ __device__ __forceinline__ void coarse_entry(const StGrid& S, const int4 rc, uin
 // Steps 2 and 3's scan for at most kSmallSort records: one workgroup sorts them in LDS, four stable 8-bit
 // passes over (key, position) with eight items per lane, then fetches what the positions stand for and scans
 // the supertile counts.  The general path is 13 launches of latency chains, 52 us for 4096 records
-// against 19 here.  At 8192 records a whole lidar call takes 301 us this way and 322 the other; twice as
-// many would not fit the LDS.
+// against 19 here.  A whole lidar call (32 x 1024 rays) takes 243 us with 8192 records and, the other way,
+// 270 with 8193; with 16 items per lane, whose registers spill, 12000 records take 313 us against 304 the
+// other way and 16384 records 361 against 345.
 // ITEMS records per lane: the ranks of a lane's items follow each other, so that fewer are faster.
 constexpr int kSmallWaves = 16, kSmallItems = 8;
 constexpr int kSmallSort = kSmallWaves * 64 * kSmallItems;
 
 template <bool PACKED, int ITEMS>
 __global__ __launch_bounds__(64 * kSmallWaves) void k_small_sort(const uint64_t* __restrict__ kin,
-                                                                 const uint32_t* __restrict__ vin, uint64_t* __restrict__ kout,
+                                                                 const uint32_t* __restrict__ vin,
+                                                                 uint64_t* __restrict__ kout,
                                                                  uint32_t* __restrict__ vout, int rec_bits,
-                                                                 int64_t* __restrict__ coff, int64_t* __restrict__ scalars,
-                                                                 int64_t cap) {
+                                                                 int64_t* __restrict__ coff,
+                                                                 int64_t* __restrict__ scalars, int64_t cap) {
   constexpr int kCap = kSmallWaves * 64 * ITEMS;
   __shared__ uint64_t s_item[kCap];                  // key | position << 32
   __shared__ uint32_t s_count[kSmallWaves][kRadixBins];    // a wavefront's running counts, then its offsets
@@ -731,7 +737,8 @@ __global__ __launch_bounds__(256) void k_coarse_emit(const DevSensor* __restrict
   const int64_t n_vis = scalars[kScVisible] < n_cap ? scalars[kScVisible] : n_cap;
   const int64_t tiles = (total + kRadixTile - 1) / kRadixTile;
   const int64_t per = (tiles + gridDim.x - 1) / gridDim.x;
-  const int64_t first = xcd_part((tiles + per - 1) / (per > 0 ? per : 1)) * per, end = first + per < tiles ? first + per : tiles;
+  const int64_t first = xcd_part((tiles + per - 1) / (per > 0 ? per : 1)) * per;
+  const int64_t end = first + per < tiles ? first + per : tiles;
   if (first >= end) return;   // uniform
   int64_t lo = wave_find_last(coff, 0, n_vis, first * kRadixTile);
   for (int64_t c = first; c < end; ++c) {

@@ -252,11 +252,12 @@ constexpr int64_t kFewGaussians = 1 << 18;   // one per lane is at most 16 wavef
 
 // Gradient of every touched record, 64 x GPL Gaussians per wavefront (lane l:
 // Gaussians l, l + 64, ...; the flags of one sensor's records loaded together), sensors in
-// order per Gaussian: the sum of the rasteriser's rows over the record's entries (positions [entry_base, entry_base + n_tiles) of
-// the slot array, rows whose flag is set; a long record's total sits in its first row), taken
-// in a fixed order so that the result does not depend on scheduling.  The geometric part (kNV
-// values) goes to g2d[rec] (added to the atomic part of split lidar tiles when `accumulate` and
-// bin_sort found such a tile, *split != 0), the channel part to the features gradient.
+// order per Gaussian: the sum of the rasteriser's rows over the record's entries (positions
+// [entry_base, entry_base + n_tiles) of the slot array, rows whose flag is set; a long record's
+// total sits in its first row), taken in a fixed order so that the result does not depend on
+// scheduling.  The geometric part (kNV values) goes to g2d[rec] (added to the atomic part of split
+// lidar tiles when `accumulate` and bin_sort found such a tile, *split != 0), the channel part to
+// the features gradient.
 // Untouched records have no gradient and are skipped here and in the projection adjoint.
 template <int CMAX, int GPL>
 __global__ __launch_bounds__(256) void k_slot_reduce(const DevSensor* __restrict__ sens, int count, int64_t N,

@@ -168,7 +168,8 @@ __global__ __launch_bounds__(256) void k_scan_reduce(Load ld, int64_t n, const i
 constexpr int64_t kScanFusedBlocks = 4096;
 
 // single block: exclusive scan of part[0..nb) in place, part[nb] = total.  4096 entries at a time, each
-// wavefront four consecutive rows of 64; a chain of load latencies (8160 sums in two steps 4.7 us, in 32 steps of 256 entries 17).
+// wavefront four consecutive rows of 64; a chain of load latencies (8160 sums in two steps 4.7 us, in 32
+// steps of 256 entries 17).
 constexpr int kPartialWaves = 16, kPartialRows = 4;
 
 template <typename T>
