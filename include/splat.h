@@ -559,7 +559,8 @@ int splat_lidar_decode_bwd(int64_t n_rays, const float* feat, const float* ray_a
  *   (M, b) = W_out h_2 + b_out,   I = M * F[0:3] + b            (k = 1, 2)
  * Convolutions: 3x3, stride 1, zero padding, bias, cross-correlation.  Weights are device
  * arrays in OIHW order; trained values are not needed to define the op.  Arithmetic is FP32
- * throughout (the 3x3 convolutions on the matrix cores). */
+ * throughout (the 3x3 convolutions on the matrix cores; their adjoints contract operands split into
+ * three bf16 parts, which hold all bits of an FP32 value, with FP32 sums). */
 typedef struct SplatCameraCNN {
   int32_t n_feat;             /* D_f >= 3 (F[0:3] is the colour); D_f + 3 + n_embed <= 32      */
   int32_t n_embed;            /* E, 0..8                                                       */
@@ -584,7 +585,9 @@ typedef struct SplatCameraCNNGrads {
 } SplatCameraCNNGrads;
 
 /* Workspace of the camera decoder for a width x height camera: the activations (six images of
- * 32 channels) that the adjoint reads, three gradient images and partial sums.  0 = invalid. */
+ * 32 channels) that the adjoint reads, the signs of four of them (16 bytes per pixel, which every
+ * splat_camera_decode writes), three gradient images, the weights in the kernels' order and partial
+ * sums.  0 = invalid. */
 size_t splat_camera_decode_workspace_bytes(int32_t width, int32_t height);
 /* Decodes one camera: feat [H*W, C] (C = cam->n_channels, or n_feat when that is 0; rows as the
  * camera rasteriser writes them) -> image [H*W, 3].  Writes the activations into ws (caller-
