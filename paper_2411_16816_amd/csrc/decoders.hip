@@ -362,7 +362,6 @@ void k_lidar_decode_bwd(int64_t n, const float* __restrict__ feat, const float* 
     }
   }
   float* dst = partial + (int64_t)blockIdx.x * n_out;
-  dec_store_sums<CM>(dst, C, lane, acc, gb0, gb1);
   // W2: the sums over the 32 lanes of each half (the two halves hold different hidden units)
 #pragma unroll
   for (int i = 0; i < 32; ++i) {
@@ -370,6 +369,7 @@ void k_lidar_decode_bwd(int64_t n, const float* __restrict__ feat, const float* 
     for (int o = 16; o >= 1; o >>= 1) gw2[i] += __shfl_xor(gw2[i], o, 64);
     if ((lane & 31) == 0) dst[nb1 + kDecHidden * (i >> 4) + dec_hidden(i & 15, half)] = gw2[i];
   }
+  dec_store_sums<CM>(dst, C, lane, acc, gb0, gb1);
 }
 
 // ---- the adjoint at 8 channels on the vector units --------------------------------------------
@@ -516,12 +516,12 @@ void k_lidar_decode_bwd_valu(int64_t n, const float* __restrict__ feat, const fl
     }
   }
   float* dst = partial + (int64_t)blockIdx.x * n_out;
-  dec_store_sums<CM>(dst, C, lane, acc, gb0, gb1);
   // W2: one value per lane after the wavefront's reduce-scatter
   bool store;
   const int slot = scatter_slot<2 * kDecHidden>(lane, store);
   const float w2sum = wave_reduce_scatter<2 * kDecHidden>(gw2);
   if (store) dst[nb1 + slot] = w2sum;
+  dec_store_sums<CM>(dst, C, lane, acc, gb0, gb1);
 }
 
 // weight gradients (+=) from the column sums of the workgroups' partials
