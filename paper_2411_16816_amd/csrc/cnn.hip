@@ -136,15 +136,15 @@ struct ConvArgs {
 };
 
 // B operand element: the weight taking input channel `cin` of the convolution's input to its
-// output channel `cout` at tap (ky, kx); zero outside the weight's channels.
+// output channel `cout` at tap (ky, kx); zero outside the weight's channels (a select, not a branch
+// around each load).
 __device__ __forceinline__ float conv_w(const ConvArgs& a, int cin, int cout, int ky, int kx) {
-  if (!a.transpose) {
-    if (cin >= a.ci_n || cout >= a.co_n) return 0.f;
-    return a.w[((cout * a.ci_n + cin) * 3 + ky) * 3 + kx];
-  }
   // input gradient: the input holds gradients of the layer's outputs (co), the output its inputs (ci)
-  if (cin >= a.co_n || cout >= a.ci_n) return 0.f;
-  return a.w[((cin * a.ci_n + cout) * 3 + (2 - ky)) * 3 + (2 - kx)];
+  const int co = a.transpose ? cin : cout, ci = a.transpose ? cout : cin;
+  const int tap = a.transpose ? 8 - (3 * ky + kx) : 3 * ky + kx;
+  const bool ok = co < a.co_n && ci < a.ci_n;
+  const float w = a.w[ok ? (co * a.ci_n + ci) * 9 + tap : 0];
+  return ok ? w : 0.f;
 }
 
 constexpr int kFrag = 9 * 16 * 64;           // A fragments of one convolution: [tap][quad][lane][4]
@@ -592,6 +592,7 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
     float red[9 * kCC * kCC];
     float b[16 * 8][2][4];
   } sm;
+  __shared__ int s_bad;   // a sum is not finite
   const int tiles_x = (W + kTS - 1) / kTS, tiles_y = (H + kWTH - 1) / kWTH;
   const int n_tiles = tiles_x * tiles_y;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -650,6 +651,7 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
       });
     }
   };
+  if (tid == 0) s_bad = 0;
   load(blockIdx.x);   // the grid has at most n_tiles workgroups
   stage(sm.t[0]);
   load(blockIdx.x + gridDim.x);
@@ -701,7 +703,8 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
     bad = SPLAT_FMA(s, 0.f, bad);
     dst[i] = s;
   }
-  __syncthreads();
+  if (bad != 0.f) s_bad = 1;
+  __syncthreads();   // all of dst is stored
   if (is_dy) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) sm.b[col * 8 + q][part][c] = accb[c];
@@ -712,7 +715,7 @@ void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ dy, 
     for (int c = 0; c < 16; ++c) s += sm.b[c * 8 + (tid >> 2)][0][tid & 3] + sm.b[c * 8 + (tid >> 2)][1][tid & 3];
     dst[9 * kCC * kCC + tid] = s;
   }
-  if (__syncthreads_or(bad != 0.f)) wgrad_fp32(x, dy, H, W, dst);   // all of dst is stored
+  if (s_bad) wgrad_fp32(x, dy, H, W, dst);
 }
 
 // dW (OIHW, +=) and db (+=) of one convolution from the column sums of the partials
