@@ -209,13 +209,12 @@ struct DecRows {
   float dpre[kDecHidden][kDecChunk + 4];
 };
 
-// A workgroup's sums of W1, b1 (blocks of the contraction over its rays) and b2 (per lane) to its row of
-// partial sums.
+// A workgroup's sums to its row of partial sums: W1 and b1 (the blocks of the contraction over its rays)
 template <int CM>
-__device__ __forceinline__ void dec_store_sums(float* __restrict__ dst, int C, int lane,
-                                               const decx4 (&acc)[2 * dec_xtiles<CM>()], float gb0, float gb1) {
+__device__ __forceinline__ void dec_store_first(float* __restrict__ dst, int C, int lane,
+                                                const decx4 (&acc)[2 * dec_xtiles<CM>()]) {
   constexpr int NXT = dec_xtiles<CM>(), NT = 2 * NXT;
-  const int XC = C + 3, nw1 = kDecHidden * XC, nw2 = nw1 + 3 * kDecHidden, li = lane & 15, lk = lane >> 4;
+  const int XC = C + 3, nw1 = kDecHidden * XC, li = lane & 15, lk = lane >> 4;
   // D[i][j] of a block: lane j + 16 (i / 4), element i % 4
 #pragma unroll
   for (int b = 0; b < NT; ++b) {
@@ -229,6 +228,11 @@ __device__ __forceinline__ void dec_store_sums(float* __restrict__ dst, int C, i
       else if (col == CM + 3) dst[nw1 + j] = v;                               // b1
     }
   }
+}
+
+// ... and b2 (a sum per lane)
+__device__ __forceinline__ void dec_store_b2(float* __restrict__ dst, int C, int lane, float gb0, float gb1) {
+  const int nw2 = kDecHidden * (C + 3) + 3 * kDecHidden;
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     gb0 += __shfl_xor(gb0, o, 64);
@@ -362,6 +366,7 @@ void k_lidar_decode_bwd(int64_t n, const float* __restrict__ feat, const float* 
     }
   }
   float* dst = partial + (int64_t)blockIdx.x * n_out;
+  dec_store_first<CM>(dst, C, lane, acc);
   // W2: the sums over the 32 lanes of each half (the two halves hold different hidden units)
 #pragma unroll
   for (int i = 0; i < 32; ++i) {
@@ -369,7 +374,7 @@ void k_lidar_decode_bwd(int64_t n, const float* __restrict__ feat, const float* 
     for (int o = 16; o >= 1; o >>= 1) gw2[i] += __shfl_xor(gw2[i], o, 64);
     if ((lane & 31) == 0) dst[nb1 + kDecHidden * (i >> 4) + dec_hidden(i & 15, half)] = gw2[i];
   }
-  dec_store_sums<CM>(dst, C, lane, acc, gb0, gb1);
+  dec_store_b2(dst, C, lane, gb0, gb1);
 }
 
 // ---- the adjoint at 8 channels on the vector units --------------------------------------------
@@ -516,12 +521,13 @@ void k_lidar_decode_bwd_valu(int64_t n, const float* __restrict__ feat, const fl
     }
   }
   float* dst = partial + (int64_t)blockIdx.x * n_out;
+  dec_store_first<CM>(dst, C, lane, acc);
   // W2: one value per lane after the wavefront's reduce-scatter
   bool store;
   const int slot = scatter_slot<2 * kDecHidden>(lane, store);
   const float w2sum = wave_reduce_scatter<2 * kDecHidden>(gw2);
   if (store) dst[nb1 + slot] = w2sum;
-  dec_store_sums<CM>(dst, C, lane, acc, gb0, gb1);
+  dec_store_b2(dst, C, lane, gb0, gb1);
 }
 
 // weight gradients (+=) from the column sums of the workgroups' partials
